@@ -19,11 +19,22 @@
 // One workgroup per position.  The s-integral uses 13 panels with edges 0 and
 // 2^-6 .. 2^6 (fine near s = 0, where a thin disc's force turns over), each with
 // an 8-point Gauss-Legendre rule; the azimuth average is the 128-point
-// trapezoid rule (periodic integrand).  The lanes own (s, phi) node pairs and
-// evaluate the force at the five radii; the workgroup adds the partial sums by
+// trapezoid rule (periodic integrand).  Every component is symmetric under
+// x -> -x and y -> -y, so the 128 azimuths hold 33 distinct ones (weight 2 on
+// the axes, 4 between them), and the axisymmetric components take one
+// evaluation per (s, radius).  The lanes own (s, phi) node pairs of the bars
+// and evaluate them at the five radii; the workgroup adds the partial sums by
 // a fixed tree.
+//
+// Bound by FP64 vector issue in the bar's 32 quadrature nodes.  Each node takes
+// one reciprocal square root refined to FP64 (its three divisions follow from
+// the square of it) instead of an IEEE square root and seven divisions, and
+// the confocal coordinate lam of a radius starts from its neighbour's.
+// 7,500 positions of the barred model: 60.1 ms with 128 azimuths of the whole
+// potential and IEEE divisions, 4.0 ms now.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -34,24 +45,117 @@ namespace sw {
 namespace {
 
 constexpr int kJnThreads = 256;
+// Up to this many positions (one workgroup per CU at most) a position takes
+// 1,024 threads: with 256 each SIMD would hold one wave and wait out its latencies
+// (250 positions of the barred model: 210 us with 256 threads, 173 with 1,024; 400:
+// 329 and 311; 700: 456 and 459; 7,500: 4.00 ms and 4.43).
+constexpr int kJnWide = 256;
 constexpr int kJnQ = 8;
 constexpr int kJnPanels = 13;
 constexpr int kJnS = kJnQ * kJnPanels;
 constexpr int kJnPhi = 128;
+constexpr int kJnQuad = kJnPhi / 4 + 1;  // distinct azimuths, 0 .. pi/2
 constexpr int kJnSums = 6;  // sigma_z^2 integrals at R - h, R - h/2, R, R + h/2, R + h; F_R at (R, z)
 
 struct JeansK {
   double hR, hz, b;
   double gt[kJnQ], gw[kJnQ];  // Gauss-Legendre rule on [-1, 1]
+  int32_t n_all;              // components; the axisymmetric ones come first (P.n_comp of them)
 };
 
 __device__ __forceinline__ double panel_edge(int k) { return k == 0 ? 0.0 : ldexp(1.0, k - 7); }
 
-template <bool NB>
-__global__ __launch_bounds__(kJnThreads) void k_jeans(PotK P, JeansK K, const double* __restrict__ pos,
+// node j of the s-integral and its weight (e^-s included)
+__device__ __forceinline__ double s_node(const JeansK& K, int j, double& ws) {
+  const int pj = j / kJnQ, q = j % kJnQ;
+  const double e0 = panel_edge(pj), e1 = panel_edge(pj + 1);
+  const double half = 0.5 * (e1 - e0), s = 0.5 * (e0 + e1) + half * K.gt[q];
+  ws = half * K.gw[q] * exp(-s);
+  return s;
+}
+
+// reciprocal and reciprocal square root in FP64: the hardware estimate (about
+// 2^-23) and one third-order step, which leaves about 2^-65
+__device__ __forceinline__ double rcp3(double v) {
+  const double r = __builtin_amdgcn_rcp(v), e = fma(-v, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+__device__ __forceinline__ double rsq3(double v) {
+  const double r = __builtin_amdgcn_rsq(v), e = fma(-v * r, r, 1.0);
+  return fma(r * e, fma(0.375, e, 0.5), r);
+}
+
+// Force of a Ferrers bar (ALL: g[0..2], else g[2] alone is formed) by the
+// 32-node rule of ferrers_f64.  lam < 0: Newton from the left bracket; else from
+// that value: m^2(lam) is convex and decreasing, so a step from the right of the
+// root lands left of it and the next ones rise.  A step below 1e-9 of
+// A_min + lam is the last (the error after it is of the order of its square).
+template <bool ALL>
+__device__ __forceinline__ void ferrers_bar(const CompK& C, const double* gq, const double* gw, double x, double y,
+                                            double z, double& lam, double* g) {
+  const double A0 = C.c[0], A1 = C.c[1], A2 = C.c[2];
+  const double x2 = x * x, y2 = y * y, z2 = z * z;
+  bool right = lam > 0.0;  // the start may lie right of the root
+  if (!(lam >= 0.0)) lam = fmax(0.0, x2 + y2 + z2 - C.c[6]);
+  for (int it = 0; it < 60; ++it) {
+    const double i0 = rcp3(A0 + lam), i1 = rcp3(A1 + lam), i2 = rcp3(A2 + lam);
+    const double t0 = x2 * i0, t1 = y2 * i1, t2 = z2 * i2;
+    const double f = t0 + t1 + t2 - 1.0;
+    if (!(f > 0.0) && !right) break;
+    const double d = f * rcp3(t0 * i0 + t1 * i1 + t2 * i2), nl = fmax(0.0, lam + d);
+    const bool last = !(fabs(nl - lam) > 1e-9 * (C.c[3] + lam));
+    right = false;
+    lam = nl;
+    if (last) break;
+  }
+  const double K = C.c[3] + lam, iK = rcp3(K);
+  const double D0 = (A0 + lam) * iK, D1 = (A1 + lam) * iK, D2 = (A2 + lam) * iK;
+  const double xs = x2 * iK, ys = y2 * iK, zs = z2 * iK;
+  double F0 = 0.0, F1 = 0.0, F2 = 0.0;
+#pragma unroll 4
+  for (int n = 0; n < kGL64; ++n) {
+    const double q = gq[n], W = gw[n];
+    const double e0 = D0 + q, e1 = D1 + q, e2 = D2 + q;
+    const double e12 = e1 * e2, e02 = e0 * e2, e01 = e0 * e1;
+    const double s = rsq3(e0 * e12), iP = s * s;
+    const double w = fmax(fma(-iP, xs * e12 + ys * e02 + zs * e01, 1.0), 0.0);
+    const double c = (W * s) * (w * w) * iP;
+    if (ALL) {
+      F0 = fma(c, e12, F0);
+      F1 = fma(c, e02, F1);
+    }
+    F2 = fma(c, e01, F2);
+  }
+  const double sc = C.c[4] * iK * rsq3(K);
+  if (ALL) {
+    g[0] -= sc * x * F0;
+    g[1] -= sc * y * F1;
+  }
+  g[2] -= sc * z * F2;
+}
+
+// force of the components that are not axisymmetric, added into g
+template <bool NB, bool ALL>
+__device__ __forceinline__ void bars_accel(const PotK& P, int n_all, double x, double y, double z, double& lam,
+                                           double* g) {
+  for (int i = P.n_comp; i < n_all; ++i) {
+    const CompK& C = P.comp[i];
+    if (C.kind == SW_FERRERS2) {
+      double l = i == P.n_comp ? lam : -1.0;  // the first bar's lam carries over from radius to radius
+      ferrers_bar<ALL>(C, P.gq64, P.gw64, x, y, z, l, g);
+      if (i == P.n_comp) lam = l;
+    } else if constexpr (NB) {
+      if (C.kind == SW_DA_T3) needle_bar<double, 3, kGL64>(C.c, P.gq64, P.gw64, x, y, z, nullptr, g);
+      else needle_bar<double, 5, kGL64>(C.c, P.gq64, P.gw64, x, y, z, nullptr, g);
+    }
+  }
+}
+
+template <bool NB, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_jeans(PotK P, JeansK K, const double* __restrict__ pos,
                                                        const double* __restrict__ eps, int64_t n,
                                                        double* __restrict__ mom, double* __restrict__ ics) {
-  __shared__ double red[kJnSums][kJnThreads];
+  __shared__ double red[kJnSums][THREADS];
   const int64_t i = blockIdx.x;
   const int tid = threadIdx.x;
   const double x = pos[i], y = pos[n + i], z = pos[2 * n + i];
@@ -61,35 +165,53 @@ __global__ __launch_bounds__(kJnThreads) void k_jeans(PotK P, JeansK K, const do
   double acc[kJnSums];
 #pragma unroll
   for (int r = 0; r < kJnSums; ++r) acc[r] = 0.0;
-  for (int p = tid; p < kJnS * kJnPhi; p += kJnThreads) {
-    const int j = p / kJnPhi, k = p % kJnPhi;
-    const int pj = j / kJnQ, q = j % kJnQ;
-    const double e0 = panel_edge(pj), e1 = panel_edge(pj + 1);
-    const double half = 0.5 * (e1 - e0), s = 0.5 * (e0 + e1) + half * K.gt[q];
-    const double ws = half * K.gw[q] * exp(-s);
-    double sp, cp;
-    sincospi((double)k * (2.0 / kJnPhi), &sp, &cp);
-    const double zz = az + K.hz * s;
+  // the axisymmetric components: one evaluation stands for the 128 azimuths
+  if (P.n_comp > 0) {
+    for (int p = tid; p < 5 * kJnS; p += THREADS) {
+      const int r = p / kJnS;
+      double ws, g[3];
+      const double s = s_node(K, p - r * kJnS, ws);
+      const double rad = r == 0 ? radii[0] : r == 1 ? radii[1] : r == 2 ? radii[2] : r == 3 ? radii[3] : radii[4];
+      const double xv[3] = {rad, 0.0, az + K.hz * s};
+      accel_f64<false>(P, xv, g);
 #pragma unroll
-    for (int r = 0; r < 5; ++r) {
-      const double xv[3] = {radii[r] * cp, radii[r] * sp, zz};
+      for (int q = 0; q < 5; ++q) acc[q] += q == r ? kJnPhi * (ws * -g[2]) : 0.0;
+    }
+    if (tid == THREADS - 1) {
       double g[3];
-      accel_f64<NB>(P, xv, g);
-      acc[r] += ws * -g[2];
+      const double xv[3] = {R, 0.0, z};
+      accel_f64<false>(P, xv, g);
+      acc[5] += kJnPhi * g[0];
     }
   }
-  for (int k = tid; k < kJnPhi; k += kJnThreads) {
+  // the bars: (s, azimuth) pairs, then the azimuths of F_R at the position itself
+  for (int p = tid; K.n_all > P.n_comp && p < (kJnS + 1) * kJnQuad; p += THREADS) {
+    const int j = p / kJnQuad, k = p - j * kJnQuad;
     double sp, cp;
     sincospi((double)k * (2.0 / kJnPhi), &sp, &cp);
-    const double xv[3] = {R * cp, R * sp, z};
-    double g[3];
-    accel_f64<NB>(P, xv, g);
-    acc[5] += g[0] * cp + g[1] * sp;
+    const double wk = k == 0 || k == kJnQuad - 1 ? 2.0 : 4.0;
+    double lam = -1.0;
+    if (j < kJnS) {
+      double ws;
+      const double s = s_node(K, j, ws);
+      const double zz = az + K.hz * s;
+      ws *= wk;
+#pragma unroll
+      for (int r = 0; r < 5; ++r) {
+        double g[3] = {0.0, 0.0, 0.0};
+        bars_accel<NB, false>(P, K.n_all, radii[r] * cp, radii[r] * sp, zz, lam, g);
+        acc[r] += ws * -g[2];
+      }
+    } else {
+      double g[3] = {0.0, 0.0, 0.0};
+      bars_accel<NB, true>(P, K.n_all, R * cp, R * sp, z, lam, g);
+      acc[5] += wk * (g[0] * cp + g[1] * sp);
+    }
   }
 #pragma unroll
   for (int r = 0; r < kJnSums; ++r) red[r][tid] = acc[r];
   __syncthreads();
-  for (int st = kJnThreads / 2; st > 0; st >>= 1) {
+  for (int st = THREADS / 2; st > 0; st >>= 1) {
     if (tid < st) {
 #pragma unroll
       for (int r = 0; r < kJnSums; ++r) red[r][tid] += red[r][tid + st];
@@ -195,12 +317,22 @@ extern "C" int jeans_ics(const sw_potential* pot, const double* pos, const doubl
   K.hR = h_R;
   K.hz = h_z;
   K.b = b;
+  K.n_all = P.n_comp;
+  // axisymmetric components first
+  const auto axisym = [](const CompK& c) {
+    return c.kind != SW_FERRERS2 && c.kind != SW_DA_T3 && c.kind != SW_DA_V4;
+  };
+  P.n_comp = (int32_t)(std::stable_partition(P.comp, P.comp + K.n_all, axisym) - P.comp);
   gl_rule(kJnQ, K.gt, K.gw);
   hipStream_t st = (hipStream_t)stream;
   if (nb)
-    hipLaunchKernelGGL(k_jeans<true>, dim3((unsigned)n), dim3(kJnThreads), 0, st, P, K, pos, eps, n, moments, ics);
+    hipLaunchKernelGGL((k_jeans<true, kJnThreads>), dim3((unsigned)n), dim3(kJnThreads), 0, st, P, K, pos, eps, n,
+                       moments, ics);
+  else if (n <= kJnWide)
+    hipLaunchKernelGGL((k_jeans<false, 1024>), dim3((unsigned)n), dim3(1024), 0, st, P, K, pos, eps, n, moments, ics);
   else
-    hipLaunchKernelGGL(k_jeans<false>, dim3((unsigned)n), dim3(kJnThreads), 0, st, P, K, pos, eps, n, moments, ics);
+    hipLaunchKernelGGL((k_jeans<false, kJnThreads>), dim3((unsigned)n), dim3(kJnThreads), 0, st, P, K, pos, eps, n,
+                       moments, ics);
   SW_HIP(hipGetLastError());
   return SW_OK;
 }

@@ -62,6 +62,30 @@ def test_barred_model_matches_oracle(gpu):
     assert np.allclose(ics_g[3:], ics_o[3:], rtol=0, atol=1e-4 + 1e-6 * np.abs(ics_o[3:]).max())
 
 
+@pytest.mark.parametrize("comps", [
+    W.BARRED["components"],
+    [("ferrers2", (1e10, 4.0, 1.5, 1.0)), ("plummer", (2e10, 0.6)), ("ferrers2", (5e9, 1.0, 2.5, 0.7)),
+     ("isochrone", (1e11, 3.0))],
+    [("ferrers2", (1e10, 4.0, 1.5, 1.0))],
+])
+def test_workgroup_widths_and_component_orders(gpu, comps):
+    """257 positions (one more than the wide workgroups take) against the same positions in calls of 256 and 1, the
+    first few against the oracle; bars before, between and without axisymmetric components.
+
+    The two widths add the same terms in another order: about 1e4 roundings of 1e-16 in each sigma_z^2, which the
+    difference quotient multiplies by R / h = 500 at most, so 1e-9 of the dispersion squared bounds <v_phi^2> and its
+    root moves by at most sqrt(1e-9) sigma where it vanishes."""
+    pos, eps = W.disc_positions(257, seed=11)
+    mom, ics = gpu_jeans(comps, pos, eps)
+    for a, b in ((0, 256), (256, 257)):
+        m2, i2 = gpu_jeans(comps, pos[:, a:b], eps[:, a:b])
+        assert np.allclose(m2[[0, 1, 2, 4]], mom[[0, 1, 2, 4], a:b], rtol=1e-10, atol=0)
+        assert np.all(np.abs(m2[3] ** 2 - mom[3, a:b] ** 2) <= 1e-9 * (mom[0, a:b] ** 2 + mom[4, a:b] ** 2))
+        assert np.array_equal(i2[:3], ics[:3, a:b])
+    mom_o, _ = O.jeans_ics(O.make_pot(comps), pos[:, :3], eps[:, :3], HR, HZ)
+    _check(mom[:, :3], mom_o)
+
+
 def test_point_mass_axis_closed_form(gpu):
     """sigma_z^2 on the axis of a point mass: GM [1/z - e^(z/h_z) E1(z/h_z) / h_z]."""
     M = 1e10
