@@ -48,6 +48,41 @@ def test_forward_backward_vs_fp64(gpu, B):
         o += k
 
 
+@pytest.mark.parametrize("B,shift", [(15, 0), (16, 1), (17, 3), (33, 2), (130, 1), (2049, 0)])
+def test_batch_edges_and_unaligned_buffers(gpu, B, shift):
+    """Batches around the 16 samples of a workgroup and the 128 in flight of the gradient products, with every buffer
+    `shift` floats off its allocation (the kernels' wide loads need no more than 4-byte alignment), and two backward
+    passes after one forward.  fp32 sums of at most 2,049 terms: 2,049 x 2^-24 = 1.2e-4 is their worst case, the
+    1e-5 taken here about 8 times their random-walk error sqrt(2049) 2^-24."""
+    import torch
+    P = lib()
+    rng = np.random.default_rng(B)
+    p, x, dy = L.init(3), rng.uniform(-1, 1, size=(B, 12)), rng.normal(size=B)
+    y_o, cache = L.forward(p, x)
+    g_o = L.backward(p, cache, dy)
+
+    def off(a):
+        t = torch.zeros(a.size + shift, device="cuda")
+        t[shift:] = _dev(a.reshape(-1))
+        return t[shift:].view(*a.shape)
+
+    pt, xt, dyt = off(p), off(x), off(dy)
+    y, g = off(np.full(B, np.nan)), off(np.full(p.size, np.nan))
+    ws = torch.full((P.mlp_workspace_bytes(B) + 4 * shift,), 255, dtype=torch.uint8, device="cuda")[4 * shift:]
+    P.mlp_forward(pt, xt, y, ws)
+    P.mlp_backward(pt, xt, off(rng.normal(size=B)), g, ws)
+    P.mlp_backward(pt, xt, dyt, g, ws)
+    torch.cuda.synchronize()
+    yg, gg = y.cpu().numpy().astype(np.float64), g.cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(yg - y_o)) <= 1e-5 * max(1.0, np.max(np.abs(y_o)))
+    o = 0
+    for name, s in L.SHAPES:
+        k = int(np.prod(s))
+        assert np.linalg.norm(gg[o:o + k] - g_o[o:o + k]) <= 1e-5 * np.linalg.norm(g_o[o:o + k]) + 1e-6 * np.linalg.norm(
+            g_o), name
+        o += k
+
+
 def test_adam_step_vs_oracle(gpu):
     import torch
     P = lib()
