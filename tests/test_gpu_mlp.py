@@ -116,6 +116,27 @@ def test_bf16_inference_close_to_fp32(gpu):
     assert err.max() < 3e-2 * max(1.0, np.abs(y_o).max())
 
 
+@pytest.mark.parametrize("B,shift", [(1, 0), (15, 1), (16, 0), (17, 3), (32, 2), (1000, 1)])
+def test_bf16_inference_batch_edges(gpu, B, shift):
+    """Batches around the 16 samples of a workgroup, buffers `shift` elements off their allocation, against the FP64
+    network with the bf16-rounded parameters: fp32 sums of 256 terms, so 256 x 2^-24 = 1.5e-5 of the largest output
+    bounds each layer and 5e-5 the three."""
+    import torch
+    P = lib()
+    rng = np.random.default_rng(B)
+    p = L.init(6)
+    x = rng.uniform(-1, 1, size=(B, 12)).astype(np.float32)
+    packed = torch.empty(p.size + shift, dtype=torch.bfloat16, device="cuda")[shift:]
+    P.mlp_pack_bf16(_dev(p), packed)
+    xt = torch.empty(B * 12 + shift, device="cuda")[shift:].view(B, 12)
+    xt.copy_(_dev(x))
+    y = torch.full((B + shift,), float("nan"), device="cuda")[shift:]
+    P.mlp_infer_bf16(packed, xt, y)
+    torch.cuda.synchronize()
+    y_o, _ = L.forward(packed.cpu().float().numpy().astype(np.float64), x.astype(np.float64))
+    assert np.max(np.abs(y.cpu().numpy() - y_o)) <= 5e-5 * max(1.0, np.abs(y_o).max())
+
+
 def test_training_lowers_loss(gpu):
     import torch
     P = lib()
