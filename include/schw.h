@@ -342,10 +342,10 @@ size_t chi2_workspace_bytes(int64_t n_con);
  * chi2_noalloc: chi2 for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc).  Same arguments and result as chi2 without the workspace: the
- * scratch (partial column sums, the model values and the result, 16.5 MiB) is a
+ * scratch (partial column sums and the sums of the squared residuals, 16.5 MiB) is a
  * static device array of the library that each GPU holds until the process
- * ends.  No device memory is allocated or freed.  The sums are split over 32
- * orbit slabs instead of chi2's 256, so the two agree to rounding, not bit for
+ * ends.  No device memory is allocated or freed.  The sums are split over at most
+ * 32 orbit slabs instead of chi2's 256, so the two agree to rounding, not bit for
  * bit.  Limit: n_con <= chi2_noalloc_max_con() (65,536); larger problems return
  * SW_EINVAL.  Every call on a GPU uses that GPU's one array: calls that overlap
  * on one GPU (several streams or threads) race and must be serialised by the

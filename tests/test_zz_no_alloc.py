@@ -39,6 +39,32 @@ def test_chi2_noalloc_matches_chi2(gpu, dtype):
         assert whole == pytest.approx(P.chi2(A, w, d, s, 0, nc, ws), rel=1e-12)
 
 
+@pytest.mark.parametrize("n,nc,cb,ce,frac", [
+    (1, 1, 0, 1, 1.0), (7, 5, 1, 4, 0.5), (31, 130, 0, 0, 0.5), (257, 1027, 3, 1026, 1.0), (600, 513, 511, 513, 0.0),
+    (8200, 66, 1, 66, 0.3)])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_chi2_and_observables_at_the_edges(gpu, n, nc, cb, ce, frac, dtype):
+    """Columns ranges that start and end inside a lane's 16 bytes, slabs around 256 rows, no and all weights zero, a NaN
+    row of weight zero (it must not count), against NumPy in FP64: at most n + nc roundings of 2^-53 each, 1e-12."""
+    import torch
+    P = lib()
+    rng = np.random.default_rng(n + nc)
+    A = rng.uniform(0, 1, size=(n, nc)).astype(np.float32 if dtype == "f32" else np.float64)
+    w = rng.exponential(1.0, n) * (rng.random(n) < frac)
+    d, sig = rng.uniform(1, 2, nc), rng.uniform(0.1, 1, nc)
+    m = A.astype(np.float64).T @ w
+    if (w == 0).any():
+        A[np.flatnonzero(w == 0)[0]] = np.nan
+    At, wt, dt, st = (torch.from_numpy(v).to(gpu) for v in (A, w, d, sig))
+    ws = torch.full((P.chi2_workspace_bytes(nc),), 255, dtype=torch.uint8, device=gpu)
+    want = float((((m - d) / sig)[cb:ce] ** 2).sum())
+    assert P.chi2(At, wt, dt, st, cb, ce, ws) == pytest.approx(want, rel=1e-12)
+    assert P.chi2_noalloc(At, wt, dt, st, cb, ce) == pytest.approx(want, rel=1e-12)
+    out = torch.full((nc,), float("nan"), dtype=torch.float64, device=gpu)
+    P.model_observables(At, wt, out)
+    assert np.allclose(out.cpu().numpy(), m, rtol=1e-12, atol=0)
+
+
 def test_chi2_noalloc_rejects_beyond_its_limit(gpu):
     import torch
     P = lib()
