@@ -584,9 +584,12 @@ __device__ __forceinline__ double seg_dot(const TA* __restrict__ val, const uint
     QuadRaw<TA> v[U];
     u16x4 c[U];
     double wgt[U];
+    bool any[U];  // whole waves: quad rows that no lane has are skipped
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bool ok = k + (int64_t)u * S < k1;
+      any[u] = LPR < 64 || u == 0 || __ballot(ok) != 0;
+      if (!any[u]) continue;
       const int64_t ka = ok ? k + (int64_t)u * S : k;
       wgt[u] = ok ? 1.0 : 0.0;
       v[u].load(val + ka);
@@ -594,6 +597,7 @@ __device__ __forceinline__ double seg_dot(const TA* __restrict__ val, const uint
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      if (!any[u]) continue;
       double t = 0.0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) t += v[u][q] * xs[c[u][q]];
@@ -601,6 +605,113 @@ __device__ __forceinline__ double seg_dot(const TA* __restrict__ val, const uint
     }
   }
   return (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+// The same sum with the first Q quad rows of the next item loaded, and every
+// gather of the current one issued, before its products are formed: for short
+// segments in many small workgroups (k_csc_colsum's small form), where a wave
+// that takes one item after the other waits most of its time.  The loads ahead
+// are unconditional (a quad past the segment reads entry 0 and is dropped when it
+// is summed): vector-memory counters complete in order, and a load skipped on
+// some paths would make the compiler wait for the prefetched ones as well.  Quad
+// row i goes to accumulator i mod 4 as in seg_dot, so the sums are the same to the bit.
+template <typename TA, int Q>
+struct Quads {
+  QuadRaw<TA> v[Q];
+  u16x4 c[Q];
+};
+
+template <int LPR, int Q, typename TA>
+__device__ __forceinline__ void quads_load(const TA* __restrict__ val, const uint16_t* __restrict__ idx, int64_t k0,
+                                           int64_t k1, int lane, Quads<TA, Q>& s) {
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    const int64_t k = k0 + 4 * lane + (int64_t)i * 4 * LPR;
+    const int64_t ka = k < k1 ? k : 0;
+    s.v[i].load(val + ka);
+    s.c[i] = __builtin_nontemporal_load(reinterpret_cast<const u16x4*>(idx + ka));
+  }
+}
+
+// t[i] = the dot of quad i: every gather from LDS is issued before the first product
+template <int Q, typename TA>
+__device__ __forceinline__ void quad_dots(const Quads<TA, Q>& s, const double* xs, double (&t)[Q]) {
+  double x[Q][4];
+#pragma unroll
+  for (int i = 0; i < Q; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[i][q] = xs[s.c[i][q]];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    t[i] = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) t[i] += s.v[i][q] * x[i][q];
+  }
+}
+
+// the segment's sum from its first Q quad rows (s) and, when it is longer, the rest
+template <int LPR, int Q, typename TA>
+__device__ __forceinline__ double quads_use(const TA* __restrict__ val, const uint16_t* __restrict__ idx, int64_t k0,
+                                            int64_t k1, const double* xs, int lane, const Quads<TA, Q>& s) {
+  constexpr int S = 4 * LPR;  // entries per quad row of the group
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  double t[Q];
+  quad_dots<Q>(s, xs, t);
+#pragma unroll
+  for (int i = 0; i < Q; ++i) a[i & 3] += k0 + 4 * lane + (int64_t)i * S < k1 ? t[i] : 0.0;
+  // quad rows Q, Q + 1, ... four at a time
+  for (int64_t k = k0 + 4 * lane + (int64_t)Q * S; k < k1; k += 4 * S) {
+    Quads<TA, 4> r;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t ka = k + (int64_t)u * S < k1 ? k + (int64_t)u * S : k;
+      r.v[u].load(val + ka);
+      r.c[u] = __builtin_nontemporal_load(reinterpret_cast<const u16x4*>(idx + ka));
+    }
+    double tr[4];
+    quad_dots<4>(r, xs, tr);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a[(Q + u) & 3] += k + (int64_t)u * S < k1 ? tr[u] : 0.0;
+  }
+  return (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+// items p = 0 .. n - 1 of a group of LPR lanes: seg(p, beg, end) gives the bounds
+// (beg = end past the group's items), out(p, t) takes the lane-partial sum
+template <int LPR, int Q, typename TA, typename SegF, typename OutF>
+__device__ __forceinline__ void seg_pipe(const TA* __restrict__ val, const uint16_t* __restrict__ idx,
+                                         const double* xs, int lane, int n, SegF seg, OutF out) {
+  int64_t b0, e0, b1, e1;
+  Quads<TA, Q> qa, qb;  // alternating roles: a register copy would wait for the prefetched loads
+  seg(0, b0, e0);
+  quads_load<LPR, Q>(val, idx, b0, e0, lane, qa);
+  const auto step = [&](const Quads<TA, Q>& use, Quads<TA, Q>& fill, int p) {
+    seg(p + 1, b1, e1);
+    quads_load<LPR, Q>(val, idx, b1, e1, lane, fill);
+    // keep the prefetch ahead of the arithmetic (the scheduler would otherwise sink the loads below it)
+    __builtin_amdgcn_sched_barrier(0);
+    out(p, quads_use<LPR, Q>(val, idx, b0, e0, xs, lane, use));
+    b0 = b1;
+    e0 = e1;
+  };
+  for (int p = 0; p < n; p += 2) {
+    step(qa, qb, p);
+    if (p + 1 < n) step(qb, qa, p + 1);
+  }
+}
+
+// stages xs[0, len) = src[0, len) with eight loads in flight per thread
+template <int NT, typename TV>
+__device__ __forceinline__ void stage_vec(double* xs, const TV* __restrict__ src, int len) {
+  for (int j0 = threadIdx.x; j0 < len; j0 += 8 * NT) {
+    TV t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = src[j0 + u * NT < len ? j0 + u * NT : j0];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (j0 + u * NT < len) xs[j0 + u * NT] = (double)t[u];
+  }
 }
 
 // sum over the aligned group of LPR lanes (result in every lane of the group)
@@ -768,16 +879,20 @@ __device__ __forceinline__ void seg_stream_rhs(const TA* __restrict__ val, const
 // columns, problem b), column c owned by wave c mod 16, the problem's orbit
 // vector staged block by block in LDS; result in part[b][0][c] (the
 // reduction then reads a single slab)
-template <typename TA, typename TV>
-__global__ __launch_bounds__(kSpThreads) void k_csc_colsum(int64_t C, int cpw, const int64_t* __restrict__ off,
+// (NT threads, the vector's block of at most BLK entries; PIPE: the pipelined sums)
+template <typename TA, typename TV, int NT, int BLK, bool PIPE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void k_csc_colsum(int64_t C, int cpw, const int64_t* __restrict__ off,
                                                           const int64_t* __restrict__ rps, int nrb,
                                                           const int64_t* __restrict__ cptr,
                                                           const uint16_t* __restrict__ rowi,
                                                           const TA* __restrict__ val, const TV* __restrict__ v,
                                                           const double* __restrict__ par, int shared,
                                                           double* __restrict__ part) {
-  __shared__ double xs[kBlk];
+  constexpr int kWaves = NT / 64;
+  __shared__ double xs[BLK];
   __shared__ double cacc[kMaxRowsWG];
+  __shared__ int32_t sp[PIPE ? kMaxRowsWG + 1 : 1];  // segment bounds relative to the first
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int b = blockIdx.y;
   if (par[b * kPar + 5] == 0.0) return;  // converged problem: frozen
@@ -786,22 +901,41 @@ __global__ __launch_bounds__(kSpThreads) void k_csc_colsum(int64_t C, int cpw, c
   const int64_t c0 = (int64_t)blockIdx.x * cpw;
   if (c0 >= C) return;
   const int nc = (int)(C - c0 < cpw ? C - c0 : cpw);
-  for (int q = w; q < nc; q += kSpWaves)
+  for (int q = w; q < nc; q += kWaves)
     if (lane == 0) cacc[q] = 0.0;
   for (int rb = 0; rb < nrb && (int64_t)rb * brows < nb; ++rb) {
     const int64_t r0 = (int64_t)rb * brows;
     const int64_t len = nb - r0 < brows ? nb - r0 : brows;
-    __syncthreads();
-    for (int64_t j = threadIdx.x; j < len; j += kSpThreads) xs[j] = (double)v[n0 + r0 + j];
-    __syncthreads();
     const int64_t* cp = cptr + ((int64_t)(shared ? 0 : b) * nrb + rb) * (C + 1);
-    for (int q = w; q < nc; q += kSpWaves) {
+    if constexpr (PIPE) {
+      const int64_t base = cp[c0];
+      __syncthreads();
+      stage_vec<NT>(xs, v + n0 + r0, (int)len);
+      for (int q = threadIdx.x; q <= nc; q += NT) sp[q] = (int32_t)(cp[c0 + q] - base);
+      __syncthreads();
+      seg_pipe<64, 4>(
+          val, rowi, xs, lane, (nc - w + kWaves - 1) / kWaves,
+          [&](int p, int64_t& beg, int64_t& end) {
+            const int q = w + p * kWaves;
+            beg = base + sp[q < nc ? q : 0];
+            end = q < nc ? base + sp[q + 1] : beg;
+          },
+          [&](int p, double t) {
+            t = wave_sum(t);
+            if (lane == 0) cacc[w + p * kWaves] += t;
+          });
+      continue;
+    }
+    __syncthreads();
+    for (int64_t j = threadIdx.x; j < len; j += NT) xs[j] = (double)v[n0 + r0 + j];
+    __syncthreads();
+    for (int q = w; q < nc; q += kWaves) {
       const int64_t c = c0 + q;
       const double t = wave_sum(seg_dot(val, rowi, cp[c], cp[c + 1], xs, lane));
       if (lane == 0) cacc[q] += t;
     }
   }
-  for (int q = w; q < nc; q += kSpWaves)
+  for (int q = w; q < nc; q += kWaves)
     if (lane == 0) part[(int64_t)b * kSlabs * C + c0 + q] = cacc[q];
 }
 
@@ -1101,12 +1235,14 @@ __global__ __launch_bounds__(kRowsBlock) void k_rowdot(const TA* __restrict__ A,
 // taken by a group of LPR lanes (64 for long rows, fewer for short ones, so
 // that a wave works on 64 / LPR rows at once); sc of problem b is staged
 // column block by column block in LDS.
-template <typename TA, int LPR>
-__global__ __launch_bounds__(kSpThreads) void k_rowdot_csr(int64_t C, int ncb, int rpw, const double* __restrict__ sc,
+// (NT threads, sc's block of at most BLK entries)
+template <typename TA, int LPR, int NT, int BLK>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void k_rowdot_csr(int64_t C, int ncb, int rpw, const double* __restrict__ sc,
                                                            RowArgs R) {
   constexpr int G = 64 / LPR;          // rows in flight per wave
-  constexpr int NS = kSpWaves * G;     // row slots of the workgroup
-  __shared__ double xs[kBlk];
+  constexpr int NS = NT / 64 * G;      // row slots of the workgroup
+  __shared__ double xs[BLK];
   __shared__ double racc[kMaxRowsWG];
   __shared__ double sums[NS][kRowSums];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1129,7 +1265,7 @@ __global__ __launch_bounds__(kSpThreads) void k_rowdot_csr(int64_t C, int ncb, i
     const int64_t c0 = (int64_t)cb * kBlk;
     const int64_t len = C - c0 < kBlk ? C - c0 : kBlk;
     __syncthreads();
-    for (int64_t j = threadIdx.x; j < len; j += kSpThreads) xs[j] = scb[c0 + j];
+    for (int64_t j = threadIdx.x; j < len; j += NT) xs[j] = scb[c0 + j];
     __syncthreads();
     for (int p = 0; p < n_pass; ++p) {
       const int r = slot + p * NS;
@@ -1792,6 +1928,27 @@ static void colsum_rhs(const Ctx& X, const TV* v) {
   else launch_colsum_rhs<TA, TV, 8>(X, v);
 }
 
+// A vector of 128 KB leaves one workgroup per CU, which then takes 16 waves.  Up
+// to kSmallVec entries several workgroups of 4 waves fit a CU and hide each other's
+// staging and barriers: taken when there are at least 1,024 of them (fewer are
+// bound by their own latency, which 16 waves shorten: one 2,000 x 1,750 problem
+// takes 7.1 and 5.8 us per row and column pass with 16 waves, 8.3 and 13.7 with 4;
+// 64 such problems 76 and 73 us with 16, 67 and 55 with 4).
+constexpr int64_t kSmallVec = 4096;
+
+static bool small_wg(int64_t len, dim3 grid) { return len <= kSmallVec && (int64_t)grid.x * grid.y >= 1024; }
+
+template <typename TA, typename TV>
+static void launch_csc_colsum(const Ctx& X, dim3 grid, int cpw, int64_t len, const TV* v) {
+  const auto go = [&](auto kernel, int nt) {
+    hipLaunchKernelGGL(kernel, grid, dim3(nt), 0, X.st, X.L.C, cpw, X.off_d, X.rps_d, X.L.nrb,
+                       X.p<int64_t>(X.L.off_cptr), X.p<uint16_t>(X.L.off_crow), X.p<TA>(X.L.off_cval), v, X.par,
+                       X.L.shared ? 1 : 0, X.p<double>(X.L.off_part));
+  };
+  if (small_wg(len, grid)) go(k_csc_colsum<TA, TV, 256, kSmallVec, true>, 256);
+  else go(k_csc_colsum<TA, TV, kSpThreads, kBlk, false>, kSpThreads);
+}
+
 template <typename TV>
 static hipError_t colsum(const Ctx& X, const TV* v) {
   if (X.dense_rhs) {
@@ -1814,25 +1971,24 @@ static hipError_t colsum(const Ctx& X, const TV* v) {
     return hipGetLastError();
   }
   if (X.sparse) {
-    // 64 columns per workgroup (several rounds of 128 KB workgroups over the
-    // 256 CUs balance the uneven column lengths); narrower groups only when
-    // that would leave CUs idle
+    // 64 columns per workgroup (several rounds of 128 KB workgroups over the 256
+    // CUs balance the uneven column lengths), fewer when that would leave CUs idle;
+    // a single large problem takes one round (each round stages every row block
+    // again: 100,000 x 48,000 takes 314 us with 192 columns, 330 with 64)
+    const int64_t one = (X.L.C * X.L.P + 255) / 256;
     int64_t cpw = 64;
-    if (X.L.C * X.L.P < 64 * 256) cpw = std::max<int64_t>(kSpWaves, (X.L.C * X.L.P + 255) / 256 / kSpWaves * kSpWaves);
+    if (one < 64) cpw = std::max<int64_t>(kSpWaves, one / kSpWaves * kSpWaves);
+    else if (X.L.P == 1 && one <= 256) cpw = (one + kSpWaves - 1) / kSpWaves * kSpWaves;
     if (g_sparse_cols > 0) cpw = g_sparse_cols;
-    dim3 grid((unsigned)((X.L.C + cpw - 1) / cpw), (unsigned)X.L.P);
-    if (X.quant)
-      hipLaunchKernelGGL((k_csc_colsum<uint16_t, TV>), grid, dim3(kSpThreads), 0, X.st, X.L.C, (int)cpw, X.off_d,
-                         X.rps_d, X.L.nrb, X.p<int64_t>(X.L.off_cptr), X.p<uint16_t>(X.L.off_crow),
-                         X.p<uint16_t>(X.L.off_cval), v, X.par, X.L.shared ? 1 : 0, X.p<double>(X.L.off_part));
-    else if (X.dtype == SW_F32)
-      hipLaunchKernelGGL((k_csc_colsum<float, TV>), grid, dim3(kSpThreads), 0, X.st, X.L.C, (int)cpw, X.off_d, X.rps_d,
-                         X.L.nrb, X.p<int64_t>(X.L.off_cptr), X.p<uint16_t>(X.L.off_crow), X.p<float>(X.L.off_cval), v,
-                         X.par, X.L.shared ? 1 : 0, X.p<double>(X.L.off_part));
-    else
-      hipLaunchKernelGGL((k_csc_colsum<double, TV>), grid, dim3(kSpThreads), 0, X.st, X.L.C, (int)cpw, X.off_d,
-                         X.rps_d, X.L.nrb, X.p<int64_t>(X.L.off_cptr), X.p<uint16_t>(X.L.off_crow),
-                         X.p<double>(X.L.off_cval), v, X.par, X.L.shared ? 1 : 0, X.p<double>(X.L.off_part));
+    int64_t len = 1;  // the longest row block
+    for (int a = 0; a < X.L.PA; ++a) {
+      const int64_t brows = slabs_per_block(X.L.rps[a]) * X.L.rps[a];
+      len = std::max(len, std::min(brows, X.L.aoff[a + 1] - X.L.aoff[a]));
+    }
+    const dim3 grid((unsigned)((X.L.C + cpw - 1) / cpw), (unsigned)X.L.P);
+    if (X.quant) launch_csc_colsum<uint16_t>(X, grid, (int)cpw, len, v);
+    else if (X.dtype == SW_F32) launch_csc_colsum<float>(X, grid, (int)cpw, len, v);
+    else launch_csc_colsum<double>(X, grid, (int)cpw, len, v);
     return hipGetLastError();
   }
   dim3 grid((unsigned)((X.L.C + kColTile - 1) / kColTile), (unsigned)kSlabs, (unsigned)X.L.P);
@@ -1882,19 +2038,27 @@ static void launch_rowdot_sparse(const Ctx& X, const RowArgs& R) {
   }
   int64_t nmax = 1;
   for (int b = 0; b < X.L.P; ++b) nmax = std::max<int64_t>(nmax, X.L.off[b + 1] - X.L.off[b]);
-  // one 128 KB workgroup per CU: rows per workgroup chosen so that a single
-  // problem fills the 256 CUs in one round (no tail round), at most 512
-  int64_t per = (nmax + 255) / 256;
+  // rows per workgroup: a single problem fills the 256 CUs in one round (no tail
+  // round), many problems give about 2,048 workgroups, each staging sc once for
+  // its rows (64 problems of 2,000 rows: 158 us with 16 rows per workgroup, 67 with
+  // 64); at most 512
+  int64_t per = std::max((nmax + 255) / 256, (X.L.N + 2047) / 2048);
   per = std::min<int64_t>(kMaxRowsWG, std::max<int64_t>(kSpWaves, (per + kSpWaves - 1) / kSpWaves * kSpWaves));
   if (g_sparse_rows > 0) per = g_sparse_rows;
   // rows with short segments (mean below 512 entries per column block) are
   // taken by 16 lanes each, four rows per wave
   const dim3 grid((unsigned)((nmax + per - 1) / per), (unsigned)X.L.P);
   const bool short_rows = g_sparse_lanes > 0 ? g_sparse_lanes == 16 : X.nnz < 512 * X.L.NA * X.L.ncb;
-  if (short_rows)
-    hipLaunchKernelGGL((k_rowdot_csr<TS, 16>), grid, dim3(kSpThreads), 0, X.st, X.L.C, X.L.ncb, (int)per, sc, R);
-  else
-    hipLaunchKernelGGL((k_rowdot_csr<TS, 64>), grid, dim3(kSpThreads), 0, X.st, X.L.C, X.L.ncb, (int)per, sc, R);
+  const auto go = [&](auto kernel, int nt) {
+    hipLaunchKernelGGL(kernel, grid, dim3(nt), 0, X.st, X.L.C, X.L.ncb, (int)per, sc, R);
+  };
+  if (small_wg(std::min<int64_t>(kBlk, X.L.C), grid)) {
+    if (short_rows) go(k_rowdot_csr<TS, 16, 256, kSmallVec>, 256);
+    else go(k_rowdot_csr<TS, 64, 256, kSmallVec>, 256);
+  } else {
+    if (short_rows) go(k_rowdot_csr<TS, 16, kSpThreads, kBlk>, kSpThreads);
+    else go(k_rowdot_csr<TS, 64, kSpThreads, kBlk>, kSpThreads);
+  }
 }
 
 template <typename TA>

@@ -235,6 +235,49 @@ def test_solve_batched_matches_oracle_per_problem(gpu):
         assert abs(x_g / x_o - 1) < CHI2_TOL
 
 
+@pytest.mark.parametrize("dtype,quantum", [("f32", 0.0), ("f64", 0.0), ("f32", 1.0 / 4000)])
+def test_many_small_problems_equal_the_large_workgroups(gpu, dtype, quantum):
+    """300 ragged problems (8 to 150 orbits, one of 4,090 whose columns hold more than the 1,024 entries loaded ahead,
+    70 constraints) take the small workgroups of the compressed passes; 512 rows and columns per workgroup take the
+    large ones.  Every row and column is summed in the same order either way, so the weights are the same to the bit;
+    the first problems and the long one also meet the KKT conditions of the oracle."""
+    import torch
+    P = lib()
+    rng = np.random.default_rng(3)
+    c, td = 70, torch.float32 if dtype == "f32" else torch.float64
+    sizes = [int(v) for v in rng.integers(8, 151, size=299)] + [4090]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    n = int(off[-1])
+    A = np.where(rng.random((n, c)) < 0.28, rng.integers(1, 300, size=(n, c)), 0) / 4000.0
+    A = A.astype(np.float32 if dtype == "f32" else np.float64)
+    ds = np.stack([A[off[k]:off[k + 1]].astype(np.float64).T @ rng.exponential(1.0, sizes[k]) for k in range(300)])
+    ds = np.maximum(ds, 1e-3) * (1 + 0.02 * rng.normal(size=ds.shape))
+    sig = 0.02 * ds
+    wts = [1.0] * 300
+    At, dt, st = torch.from_numpy(A).to(gpu, td), torch.from_numpy(ds).to(gpu), torch.from_numpy(sig).to(gpu)
+    out = []
+    try:
+        for per in (0, 512):
+            P.set_tuning("sparse_rows_per_wg", per)
+            P.set_tuning("sparse_cols_per_wg", per)
+            opts = P._lib.SolveOpts()
+            opts.gram, opts.nu, opts.refine_iter, opts.quantum = 1, 1e-2, 200, quantum
+            w = torch.empty(n, dtype=torch.float64, device=gpu)
+            ws = torch.full((P.solve_batched_workspace_bytes(off, c, opts),), 255, dtype=torch.uint8, device=gpu)
+            _, reps = P.solve_weights_batched(At, off, dt, st, wts, -1.0, opts, w, ws)
+            assert reps[0].nnz > 0
+            out.append((w.cpu().numpy(), reps))
+    finally:
+        P.set_tuning("sparse_rows_per_wg", 0)
+        P.set_tuning("sparse_cols_per_wg", 0)
+    assert np.array_equal(out[0][0], out[1][0])
+    assert [r.refine_iters for r in out[0][1]] == [r.refine_iters for r in out[1][1]]
+    for k in (0, 1, 299):
+        U, y = N.scale_problem(A[off[k]:off[k + 1]].astype(np.float64), ds[k], sig[k], 1.0)
+        kkt = N.kkt_residual(U, y, out[0][1][k].mu, out[0][0][off[k]:off[k + 1]]) / np.abs(U.T @ y).max()
+        assert kkt <= 1.5 * max(out[0][1][k].kkt, 1e-7)
+
+
 def test_solve_dense_matrix_path(gpu):
     """A fully dense matrix takes the uncompressed passes over A."""
     rng = np.random.default_rng(12)
