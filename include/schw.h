@@ -538,7 +538,8 @@ int gh_fit_matrix(const void* A, int32_t dtype, int64_t n_orb, int64_t n_con, in
  *                             single-precision binned integration (each takes
  *                             half of the bar's quadrature nodes)
  *   "hist_lds_kb"             LDS budget (KiB, 4..160) of one histogram
- *                             workgroup; sets how many orbit rows it carries
+ *                             workgroup that carries several orbit rows (at
+ *                             most 16 KiB are used for that)
  *   "sparse_rows_per_wg"      orbit rows per row-dot workgroup of the weight
  *                             solve's compressed passes (0: automatic, else a
  *                             multiple of 16 up to 512)

@@ -118,6 +118,27 @@ def _barred_oracle(ic64, dt64, n_steps, f32_state):
 
 
 @pytest.mark.parametrize("lanes", [1, 2])
+@pytest.mark.parametrize("n,nx,nz,nv,surface", [(4500, 3, 1, 3, 0), (6200, 5, 3, 1, 1), (2049, 1, 1, 2, 0)])
+def test_histograms_of_several_rows(gpu, n, nx, nz, nv, surface):
+    """Enough orbits that a histogram workgroup carries several rows (more than 2,048 of them), blocks of odd cell
+    counts whose last store is partial and whose rows are not 16-byte aligned, with and without the surface block:
+    the FP64 matrix equals the oracle's, the FP32 one holds whole counts that sum with the overflow to one."""
+    obs = dict(W.SMALL["obs"], nx=nx, ny=5, nz=nz, npx=7, npy=1, nv=nv, surface=surface, upsilon=2.5)
+    ics, dt = W.grid_ics(W.load_table("plummer_mn"), seed=4, n_steps=1000)
+    rep = -(-n // ics.shape[1])
+    ics, dt = np.tile(ics, rep)[:, :n] * np.linspace(0.9, 1.1, n), np.tile(dt, rep)[:n]
+    n_steps = 12
+    A, ov, dr, fl = gpu_integrate(W.SMALL, ics, dt, n_steps, "f64", obs=obs)
+    c_o, ov_o, dr_o, fl_o = oracle_integrate(W.SMALL, ics, dt, n_steps, obs=obs)
+    ob = O.make_obs(obs, O.euler_matrix(*W.SMALL["euler"]))
+    assert np.array_equal(A, O.time_fractions(c_o, n_steps, obs=ob))
+    assert np.array_equal(ov, ov_o / (4.0 * n_steps)) and np.array_equal(dr, dr_o) and np.array_equal(fl, fl_o)
+    A32, ov32, _, _ = gpu_integrate(W.SMALL, ics, dt, n_steps, "f32", obs=obs)
+    k = A32[:, :nx * 5 * nz + 7 * nv].astype(np.float64) * (4 * n_steps)
+    assert np.all(np.abs(k - np.rint(k)) <= 1e-5 * np.maximum(k, 1))
+    assert np.allclose(np.rint(k)[:, :nx * 5 * nz].sum(1) + ov32[:, 0] * 4 * n_steps, 4 * n_steps, atol=1e-9)
+
+
 def test_barred_fp32_subsample_vs_fp64_oracle(gpu, lanes):
     """Barred model (MN + Ferrers + flattened NFW, 40 km/s/kpc) in FP32 against the
     FP64 oracle on the seeded 1,000-orbit subsample of the 100,000-orbit library,
