@@ -117,7 +117,6 @@ def _barred_oracle(ic64, dt64, n_steps, f32_state):
     return _ORACLE_CACHE[key]
 
 
-@pytest.mark.parametrize("lanes", [1, 2])
 @pytest.mark.parametrize("n,nx,nz,nv,surface", [(4500, 3, 1, 3, 0), (6200, 5, 3, 1, 1), (2049, 1, 1, 2, 0)])
 def test_histograms_of_several_rows(gpu, n, nx, nz, nv, surface):
     """Enough orbits that a histogram workgroup carries several rows (more than 2,048 of them), blocks of odd cell
@@ -139,6 +138,7 @@ def test_histograms_of_several_rows(gpu, n, nx, nz, nv, surface):
     assert np.allclose(np.rint(k)[:, :nx * 5 * nz].sum(1) + ov32[:, 0] * 4 * n_steps, 4 * n_steps, atol=1e-9)
 
 
+@pytest.mark.parametrize("lanes", [1, 2])
 def test_barred_fp32_subsample_vs_fp64_oracle(gpu, lanes):
     """Barred model (MN + Ferrers + flattened NFW, 40 km/s/kpc) in FP32 against the
     FP64 oracle on the seeded 1,000-orbit subsample of the 100,000-orbit library,
