@@ -3,7 +3,7 @@
 // after accepted step k weighs dt_k / t_total), in FP64.
 //
 // Two kernels:
-//  1. k_bs23: one orbit per lane, in double or in single precision (the
+//  1. k_bs23: one orbit per lane of an integrating wave, in double or in single precision (the
 //     single-precision force is the leapfrog integrator's: the bar's 16-node
 //     rule, hardware reciprocals); the total time is summed and the Jacobi
 //     drift evaluated in double either way.  Equations of motion in the bar frame for
@@ -14,16 +14,29 @@
 //     next k1), the embedded second-order y2 = y + h (7/24 k1 + 1/4 k2 + 1/3 k3
 //     + 1/8 k4); err = max_i |y3_i - y2_i| / (atol + rtol max(|y_i|, |y3_i|)),
 //     accepted when err <= 1, next step h min(5, max(0.2, 0.9 err^(-1/3))); 100
-//     rejections in a row end the orbit with the non-finite flag.  Every
-//     accepted step appends its mirror copies' packed cells (as the leapfrog
-//     path does) and its step to the orbit's streams.
-//  2. k_hist_w: one workgroup per orbit and column window: each event's weight
-//     dt_k / t_total is rounded to a 64-bit fixed-point integer in units of
-//     2^-52 and added into an LDS histogram of integers, written as
-//     sum / (copies 2^52) (divided by Upsilon for the surface block).  Integer
-//     adds are exact, so the result does not depend on the order in which the
-//     lanes add (repeated runs are identical to the bit); the rounding moves
-//     each weight by at most 2^-53, under 1e-12 of an entry over 5,000 steps.
+//     rejections in a row end the step (length 0) with the non-finite flag.
+//     Every accepted step appends its mirror copies' packed cells (as the
+//     leapfrog path does) and its step to the orbit's streams.
+//     Bound by the serial chain of an attempt (three forces, the error norm, a
+//     power): 30,000 orbits are 469 waves for 1,024 SIMDs.  So (a) every lane
+//     takes its own attempts, whether or not its neighbours' were accepted (a
+//     wave that repeats a step until all 64 lanes accept takes more attempts than
+//     any of them), and (b) what does not feed the next
+//     attempt is done by three other waves of the workgroup, one binning and two
+//     evaluating the Jacobi drift (half of the orbits each, two steps of an orbit
+//     at a time), from states handed over in LDS, kRound attempts at a time.  Each lane's arithmetic is the same as in one wave.
+//     30,000 x 5,000 steps of the barred model in FP32: 107.5 ms in one wave with
+//     common steps, 46.7 now (54.9 with one drift wave).
+//  2. k_hist_w: one workgroup per orbit (and window of columns when a row does
+//     not fit LDS): each event's weight dt_k / t_total is rounded to a 64-bit
+//     fixed-point integer in units of 2^-52 and added into an LDS histogram of
+//     integers, written as sum / (copies 2^52) (divided by Upsilon for the
+//     surface block).  Integer adds are exact, so the result does not depend on
+//     the order in which the lanes add (repeated runs are identical to the bit);
+//     the rounding moves each weight by at most 2^-53, under 1e-12 of an entry
+//     over 5,000 steps.  The three blocks of a row are one histogram, so a row of
+//     up to 20,000 columns reads its events once: 30,000 rows of 19,541 columns
+//     took 6.2 ms in five passes, 4.0 now.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -35,7 +48,9 @@
 namespace sw {
 namespace {
 
-constexpr int kBsWindow = 8000;  // histogram columns per pass (64 KB of doubles)
+constexpr int kBsWindow = 20000;  // histogram columns per pass (160,000 bytes of LDS)
+constexpr int kRound = 8;          // attempts between two hand-overs
+constexpr int kBsThreads = 256;    // the integrating, the binning and two drift waves
 
 template <bool NB>
 __device__ __forceinline__ void bs_rhs(const PotK& P, const double* y, double* f) {
@@ -86,128 +101,230 @@ __device__ __forceinline__ double bs_jacobi(const PotK& P, const float* y, float
 __device__ __forceinline__ double bs_pow(double e) { return pow(e, -1.0 / 3.0); }
 __device__ __forceinline__ float bs_pow(float e) { return powf(e, -1.0f / 3.0f); }
 
+// accepted steps handed from the integrating wave to the others
+template <typename T>
+struct BsRound {
+  T y[kRound][6][64];
+  T dt[kRound][64];
+  float lamw[kRound][64];
+  int32_t n[64];  // accepted steps of each lane in the round
+};
+
 // T: the arithmetic of the state, the stages and the step control (the total
 // time is summed in double, the Jacobi drift evaluated in double)
 template <typename T, bool NB, bool CYL>
-__global__ __launch_bounds__(64) void k_bs23(PotK P, ObsK O, const double* __restrict__ ics,
-                                              const double* __restrict__ h0, int64_t n, int32_t S, double rtol,
-                                              double atol, uint64_t* __restrict__ ev_m, uint64_t* __restrict__ ev_k,
-                                              double* __restrict__ wts, double* __restrict__ ttot,
-                                              double* __restrict__ drift, uint8_t* __restrict__ flags) {
+__global__ __launch_bounds__(kBsThreads) void k_bs23(PotK P, ObsK O, const double* __restrict__ ics,
+                                                      const double* __restrict__ h0, int64_t n, int32_t S,
+                                                      double rtol, double atol, uint64_t* __restrict__ ev_m,
+                                                      uint64_t* __restrict__ ev_k, double* __restrict__ wts,
+                                                      double* __restrict__ ttot, double* __restrict__ drift,
+                                                      uint8_t* __restrict__ flags) {
 #pragma clang fp contract(off)
-  const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= n) return;
+  __shared__ BsRound<T> rounds[2];
+  __shared__ float lam0[64];
+  __shared__ int32_t badl[64];
+  __shared__ int32_t last;  // the round after which every lane has its S steps (-1: not yet)
+  const int lane = threadIdx.x & 63, role = threadIdx.x >> 6;
+  // this lane's orbit; a drift wave's lanes l and l + 32 share one
+  const int ol = role < 2 ? lane : 32 * (role - 2) + (lane & 31);
+  const int64_t o = (int64_t)blockIdx.x * 64 + ol;
+  const bool mine = o < n;
+  const int64_t oi = mine ? o : n - 1;  // lanes past the end repeat the last orbit and write nothing
   T y[6], k1[6];
-  for (int i = 0; i < 6; ++i) y[i] = (T)ics[(int64_t)i * n + o];
+  for (int i = 0; i < 6; ++i) y[i] = (T)ics[(int64_t)i * n + oi];
   const T rt = (T)rtol, at = (T)atol;
-  T h = (T)h0[o];
-  double tt = 0.0, dmax = 0.0;
+  T h = (T)h0[oi];
   float lamw = -1.0f;
+  int s = 0, tries = 0;  // steps taken (each role counts its own), rejections in a row
+  double tt = 0.0, dmax = 0.0, E0 = 0.0;
   bool bad = false;
-  bs_rhs<NB>(P, y, k1, lamw);
-  const double E0 = bs_jacobi<NB>(P, y, lamw);
-  for (int s = 0; s < S; ++s) {
-    T dt = (T)0;
-    for (int tries = 0; tries < 100; ++tries) {
-      const T hh = h;
-      T t[6], k2[6], k3[6], y3[6], k4[6];
-      for (int i = 0; i < 6; ++i) t[i] = y[i] + (T)0.5 * hh * k1[i];
-      bs_rhs<NB>(P, t, k2, lamw);
-      for (int i = 0; i < 6; ++i) t[i] = y[i] + (T)0.75 * hh * k2[i];
-      bs_rhs<NB>(P, t, k3, lamw);
-      for (int i = 0; i < 6; ++i)
-        y3[i] = y[i] + hh * ((T)(2.0 / 9.0) * k1[i] + (T)(1.0 / 3.0) * k2[i] + (T)(4.0 / 9.0) * k3[i]);
-      bs_rhs<NB>(P, y3, k4, lamw);
-      T err = (T)0;
-      for (int i = 0; i < 6; ++i) {
-        const T y2 = y[i] + hh * ((T)(7.0 / 24.0) * k1[i] + (T)0.25 * k2[i] + (T)(1.0 / 3.0) * k3[i] +
-                                  (T)0.125 * k4[i]);
-        const T sc = at + rt * fmax(fabs(y[i]), fabs(y3[i]));
-        err = fmax(err, fabs(y3[i] - y2) / sc);
-      }
-      T fac = err > (T)0 ? (T)0.9 * bs_pow(err) : (T)5;
-      fac = fmin((T)5, fmax((T)0.2, fac));
-      h = hh * fac;
-      if (err <= (T)1) {
-        for (int i = 0; i < 6; ++i) {
-          y[i] = y3[i];
-          k1[i] = k4[i];
-        }
-        dt = hh;
-        break;
-      }
-    }
-    if (dt == (T)0) bad = true;
-    for (int i = 0; i < 6; ++i)
-      if (!isfinite(y[i])) bad = true;
-    tt += (double)dt;
-    int mc[4], kc[4];
-    cells4<T, CYL>(P, O, y, mc, kc);
-    uint64_t vm = 0, vk = 0;
-    for (int c = 0; c < 4; ++c) {
-      vm |= (uint64_t)(uint16_t)(mc[c] < 0 ? 0xFFFF : mc[c]) << (16 * c);
-      vk |= (uint64_t)(uint16_t)(kc[c] < 0 ? 0xFFFF : kc[c]) << (16 * c);
-    }
-    const int64_t e = o * S + s;
-    ev_m[e] = vm;
-    ev_k[e] = vk;
-    wts[e] = (double)dt;
-    if (O.drift_every > 0 && (s + 1) % O.drift_every == 0) {
-      const double d = fabs(bs_jacobi<NB>(P, y, lamw) / E0 - 1.0);
-      if (!(d <= dmax)) dmax = d;
-    }
+  if (role == 0) {
+    bs_rhs<NB>(P, y, k1, lamw);
+    lam0[lane] = lamw;
+    if (lane == 0) last = -1;
   }
-  ttot[o] = tt;
-  drift[o] = dmax;
-  flags[o] = (uint8_t)((!(dmax <= 0.1) ? SW_FLAG_DRIFT : 0) | (bad ? SW_FLAG_NONFINITE : 0));
+  __syncthreads();
+  if (role >= 2) E0 = bs_jacobi<NB>(P, y, lam0[ol]);
+  for (int round = 0;; ++round) {
+    if (role == 0) {
+      BsRound<T>& R = rounds[round & 1];
+      int got = 0;
+      if (last < 0) {
+        for (int a = 0; a < kRound; ++a) {
+          if (s >= S) continue;
+          const T hh = h;
+          T t[6], k2[6], k3[6], y3[6], k4[6];
+          for (int i = 0; i < 6; ++i) t[i] = y[i] + (T)0.5 * hh * k1[i];
+          bs_rhs<NB>(P, t, k2, lamw);
+          for (int i = 0; i < 6; ++i) t[i] = y[i] + (T)0.75 * hh * k2[i];
+          bs_rhs<NB>(P, t, k3, lamw);
+          for (int i = 0; i < 6; ++i)
+            y3[i] = y[i] + hh * ((T)(2.0 / 9.0) * k1[i] + (T)(1.0 / 3.0) * k2[i] + (T)(4.0 / 9.0) * k3[i]);
+          bs_rhs<NB>(P, y3, k4, lamw);
+          T err = (T)0;
+          for (int i = 0; i < 6; ++i) {
+            const T y2 = y[i] + hh * ((T)(7.0 / 24.0) * k1[i] + (T)0.25 * k2[i] + (T)(1.0 / 3.0) * k3[i] +
+                                      (T)0.125 * k4[i]);
+            const T sc = at + rt * fmax(fabs(y[i]), fabs(y3[i]));
+            err = fmax(err, fabs(y3[i] - y2) / sc);
+          }
+          T fac = err > (T)0 ? (T)0.9 * bs_pow(err) : (T)5;
+          fac = fmin((T)5, fmax((T)0.2, fac));
+          h = hh * fac;
+          const bool ok = err <= (T)1;
+          if (ok) {
+            for (int i = 0; i < 6; ++i) {
+              y[i] = y3[i];
+              k1[i] = k4[i];
+            }
+          }
+          ++tries;
+          if (ok || tries == 100) {  // a step: accepted, or of length 0 after 100 rejections
+            for (int i = 0; i < 6; ++i) R.y[got][i][lane] = y[i];
+            R.dt[got][lane] = ok ? hh : (T)0;
+            R.lamw[got][lane] = lamw;
+            ++got;
+            ++s;
+            tries = 0;
+          }
+        }
+        if (__ballot(s < S) == 0 && lane == 0) last = round;
+      }
+      R.n[lane] = got;
+    } else if (round > 0 && role == 1) {
+      const BsRound<T>& R = rounds[(round - 1) & 1];
+      const int got = R.n[lane];
+      for (int a = 0; a < kRound; ++a) {
+        if (a >= got) continue;
+        for (int i = 0; i < 6; ++i) y[i] = R.y[a][i][lane];
+        const T dt = R.dt[a][lane];
+        if (dt == (T)0) bad = true;
+        for (int i = 0; i < 6; ++i)
+          if (!isfinite(y[i])) bad = true;
+        tt += (double)dt;
+        int mc[4], kc[4];
+        cells4<T, CYL>(P, O, y, mc, kc);
+        uint64_t vm = 0, vk = 0;
+        for (int c = 0; c < 4; ++c) {
+          vm |= (uint64_t)(uint16_t)(mc[c] < 0 ? 0xFFFF : mc[c]) << (16 * c);
+          vk |= (uint64_t)(uint16_t)(kc[c] < 0 ? 0xFFFF : kc[c]) << (16 * c);
+        }
+        if (mine) {
+          const int64_t e = o * S + s;
+          ev_m[e] = vm;
+          ev_k[e] = vk;
+          wts[e] = (double)dt;
+        }
+        ++s;
+      }
+    } else if (round > 0 && O.drift_every > 0) {
+      const BsRound<T>& R = rounds[(round - 1) & 1];
+      const int got = R.n[ol];
+      for (int a0 = 0; a0 < kRound; a0 += 2) {
+        const int a = a0 + (lane >> 5);  // lanes below 32 take the earlier step of the two
+        double d = 0.0;
+        const bool on = a < got && (s + a + 1) % O.drift_every == 0;
+        if (on) {
+          for (int i = 0; i < 6; ++i) y[i] = R.y[a][i][ol];
+          d = fabs(bs_jacobi<NB>(P, y, R.lamw[a][ol]) / E0 - 1.0);
+        }
+        // both lanes keep the maximum, in the order of the steps (a NaN ends a
+        // maximum, so the order counts)
+        const double de = __shfl(d, lane & 31, 64), dl = __shfl(d, (lane & 31) + 32, 64);
+        const bool oe = __shfl((int)on, lane & 31, 64) != 0, ol2 = __shfl((int)on, (lane & 31) + 32, 64) != 0;
+        if (oe && !(de <= dmax)) dmax = de;
+        if (ol2 && !(dl <= dmax)) dmax = dl;
+      }
+      s += got;
+    }
+    __syncthreads();
+    // the rounds end with the one in which the last steps were binned.  `last` is set
+    // once, before a barrier; a wave that reads it late, in the next round, may see
+    // that round's number, which is not below its own
+    const int l = last;
+    if (l >= 0 && round > l) break;
+  }
+  if (role == 1) badl[lane] = bad ? 1 : 0;
+  __syncthreads();
+  if (!mine) return;
+  if (role == 1) ttot[o] = tt;
+  if (role >= 2 && lane < 32) {
+    drift[o] = dmax;
+    flags[o] = (uint8_t)((!(dmax <= 0.1) ? SW_FLAG_DRIFT : 0) | (badl[ol] ? SW_FLAG_NONFINITE : 0));
+  }
 }
 
-// columns [win0, win0 + wn) of one block; fold_nv > 0: surface pass (codes fold
-// to their aperture); slot >= 0 and win0 == 0: the block's overflow is written
-__global__ __launch_bounds__(256) void k_hist_w(const uint64_t* __restrict__ ev, const double* __restrict__ wts,
-                                                const double* __restrict__ ttot, int32_t S, int32_t ncopy,
-                                                int32_t ncell, int32_t win0, int32_t wn, int64_t n_con,
-                                                int32_t col_off, double* __restrict__ A,
-                                                double* __restrict__ overflow, int32_t slot, int32_t fold_nv,
-                                                int32_t fold_nkin, double div) {
+// Columns [win0, win0 + wn) of a row; the blocks' first columns are 0, n_mass and
+// n_mass + n_kin (nv > 0: surface block, kinematic codes ap nv + v_bin and
+// n_kin + ap count in its column ap).  The window 0 also writes the overflow.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_hist_w(const uint64_t* __restrict__ ev_m, const uint64_t* __restrict__ ev_k,
+                                               const double* __restrict__ wts, const double* __restrict__ ttot,
+                                               int32_t S, int32_t ncopy, int32_t n_mass, int32_t n_kin, int32_t nv,
+                                               int32_t win0, int32_t wn, int64_t n_con, double* __restrict__ A,
+                                               double* __restrict__ overflow, double div) {
   extern __shared__ unsigned long long hq[];
-  __shared__ unsigned long long ovq;
+  __shared__ unsigned long long ovq[2];
   const int64_t o = blockIdx.x;
   const int tid = threadIdx.x;
-  for (int c = tid; c < wn; c += 256) hq[c] = 0ull;
-  if (tid == 0) ovq = 0ull;
+  for (int c = tid; c < wn; c += NT) hq[c] = 0ull;
+  if (tid < 2) ovq[tid] = 0ull;
   __syncthreads();
   const double inv_t = 1.0 / ttot[o];
-  for (int s = tid; s < S; s += 256) {
-    const uint64_t v = ev[o * S + s];
-    const unsigned long long q = (unsigned long long)llrint(wts[o * S + s] * inv_t * 0x1p52);
-    for (int c = 0; c < ncopy; ++c) {
-      uint32_t idx = (uint32_t)(v >> (16 * c)) & 0xFFFFu;
-      if (fold_nv > 0 && idx != 0xFFFFu)
-        idx = idx < (uint32_t)fold_nkin ? idx / (uint32_t)fold_nv : idx - (uint32_t)fold_nkin;
-      if (idx >= (uint32_t)ncell) {
-        if (win0 == 0) atomicAdd(&ovq, q);
-      } else if (idx >= (uint32_t)win0 && idx < (uint32_t)(win0 + wn)) {
-        atomicAdd(&hq[idx - win0], q);
+  const uint32_t nm = (uint32_t)n_mass, nk = (uint32_t)n_kin, w0 = (uint32_t)win0, w1 = (uint32_t)(win0 + wn);
+  const auto add = [&](uint32_t col, unsigned long long q) {
+    if (col >= w0 && col < w1) atomicAdd(&hq[col - w0], q);
+  };
+  constexpr int U = 4;  // steps in flight
+  for (int s0 = tid; s0 < S; s0 += U * NT) {
+    uint64_t vm[U], vk[U];
+    double wt[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t e = o * S + (s0 + u * NT < S ? s0 + u * NT : s0);
+      vm[u] = ev_m[e];
+      vk[u] = ev_k[e];
+      wt[u] = wts[e];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u * NT >= S) break;
+      const unsigned long long q = (unsigned long long)llrint(wt[u] * inv_t * 0x1p52);
+      for (int c = 0; c < ncopy; ++c) {
+        const uint32_t im = (uint32_t)(vm[u] >> (16 * c)) & 0xFFFFu, ik = (uint32_t)(vk[u] >> (16 * c)) & 0xFFFFu;
+        if (im < nm) add(im, q);
+        else if (win0 == 0) atomicAdd(&ovq[0], q);
+        if (ik < nk) add(nm + ik, q);
+        else if (win0 == 0) atomicAdd(&ovq[1], q);
+        if (nv > 0 && ik != 0xFFFFu) add(nm + nk + (ik < nk ? ik / (uint32_t)nv : ik - nk), q);
       }
     }
   }
   __syncthreads();
   const double scale = 0x1p-52 / (double)ncopy;
-  double* row = A + o * n_con + col_off + win0;
-  for (int c = tid; c < wn; c += 256) row[c] = (double)hq[c] * scale / div;
-  if (tid == 0 && slot >= 0 && win0 == 0) overflow[o * 2 + slot] = (double)ovq * scale;
+  double* row = A + o * n_con + win0;
+  for (int c = tid; c < wn; c += NT) {
+    const double v = (double)hq[c] * scale;
+    row[c] = (uint32_t)(win0 + c) >= nm + nk ? v / div : v;
+  }
+  if (tid < 2 && win0 == 0) overflow[o * 2 + tid] = (double)ovq[tid] * scale;
 }
 
 size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-int hist_w(const uint64_t* ev, const double* wts, const double* ttot, int64_t n, int32_t S, int32_t ncopy,
-           int32_t ncell, int64_t n_con, int32_t col_off, double* A, double* overflow, int32_t slot, hipStream_t st,
-           int32_t fold_nv = 0, int32_t fold_nkin = 0, double div = 1.0) {
-  for (int32_t w0 = 0; w0 < ncell; w0 += kBsWindow) {
-    const int32_t wn = ncell - w0 < kBsWindow ? ncell - w0 : kBsWindow;
-    hipLaunchKernelGGL(k_hist_w, dim3((unsigned)n), dim3(256), (size_t)wn * sizeof(double), st, ev, wts, ttot, S,
-                       ncopy, ncell, w0, wn, n_con, col_off, A, overflow, slot, fold_nv, fold_nkin, div);
+// rows that leave one workgroup per CU take 1,024 threads, shorter ones 256
+int hist_w(const uint64_t* ev_m, const uint64_t* ev_k, const double* wts, const double* ttot, int64_t n, int32_t S,
+           const ObsK& O, int64_t n_con, double* A, double* overflow, double upsilon, hipStream_t st) {
+  const int32_t nv = O.surface ? O.nv : 0;
+  for (int64_t w0 = 0; w0 < n_con; w0 += kBsWindow) {
+    const int32_t wn = (int32_t)(n_con - w0 < kBsWindow ? n_con - w0 : kBsWindow);
+    const size_t lds = (size_t)wn * 8;
+    const auto go = [&](auto kernel, int nt) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(nt), lds, st, ev_m, ev_k, wts, ttot, S, O.ncopy, O.n_mass,
+                         O.n_kin, nv, (int32_t)w0, wn, n_con, A, overflow, upsilon);
+    };
+    if (lds > 64 * 1024) go(k_hist_w<1024>, 1024);
+    else go(k_hist_w<256>, 256);
     SW_HIP(hipGetLastError());
   }
   return SW_OK;
@@ -250,7 +367,7 @@ extern "C" int integrate_bs23_and_bin(const sw_potential* pot, const double* ics
   double* wts = (double*)(ws + 2 * per);
   double* ttot = (double*)(ws + 3 * per);
   hipStream_t st = (hipStream_t)stream;
-  const dim3 grid((unsigned)((n_orb + 63) / 64)), block(64);
+  const dim3 grid((unsigned)((n_orb + 63) / 64)), block(kBsThreads);
 #define SW_BS23_LAUNCH(T, NB, CYL)                                                                                \
   hipLaunchKernelGGL((k_bs23<T, NB, CYL>), grid, block, 0, st, P, O, ics, h0, n_orb, n_steps, rtol, atol, ev_m, ev_k, \
                      wts, ttot, drift, flags)
@@ -274,10 +391,5 @@ extern "C" int integrate_bs23_and_bin(const sw_potential* pot, const double* ics
 #undef SW_BS23_LAUNCH
   SW_HIP(hipGetLastError());
   const int64_t n_con = (int64_t)O.n_mass + O.n_kin + (O.surface ? O.n_ap : 0);
-  int rc = hist_w(ev_m, wts, ttot, n_orb, n_steps, O.ncopy, O.n_mass, n_con, 0, A, overflow, 0, st);
-  if (rc == SW_OK) rc = hist_w(ev_k, wts, ttot, n_orb, n_steps, O.ncopy, O.n_kin, n_con, O.n_mass, A, overflow, 1, st);
-  if (rc == SW_OK && O.surface)
-    rc = hist_w(ev_k, wts, ttot, n_orb, n_steps, O.ncopy, O.n_ap, n_con, O.n_mass + O.n_kin, A, overflow, -1, st,
-                O.nv, O.n_kin, obs->upsilon);
-  return rc;
+  return hist_w(ev_m, ev_k, wts, ttot, n_orb, n_steps, O, n_con, A, overflow, obs->upsilon, st);
 }

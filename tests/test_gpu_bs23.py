@@ -68,6 +68,31 @@ def test_small_model_matches_oracle(gpu):
     assert np.allclose(A[:, :1000].sum(1) + ov[:, 0], 1.0, rtol=0, atol=1e-12)
 
 
+@pytest.mark.parametrize("n_steps,drift_every", [(1, 1), (8, 0), (9, 3), (50, 2)])
+@pytest.mark.parametrize("precision", [1, 2])
+def test_rounds_and_bad_orbits(gpu, n_steps, drift_every, precision):
+    """Steps around the 8 attempts of a hand-over, 65 orbits (one lane of the second workgroup), one of them NaN (100
+    rejections per step, flagged) and one with a trial step that is rejected many times: in double precision the other
+    orbits agree with the oracle (bars of the small-model test), and in both the bad orbit changes no other to the bit."""
+    cfg = W.SMALL
+    obs = dict(cfg["obs"], surface=1, upsilon=2.0, drift_every=drift_every)
+    ics, dt = W.grid_ics(W.load_table(cfg["table"]), seed=7, n_steps=1000)
+    ics, dt = np.ascontiguousarray(ics[:, 100:165]), dt[100:165].copy()
+    dt[5] *= 1e4
+    A, ov, dr, fl = gpu_bs23(cfg, obs, ics, dt, n_steps, 1e-8, 1e-10, precision)
+    if precision == 2:
+        A_o, ov_o, dr_o, fl_o = oracle_bs23(cfg, obs, ics, dt, n_steps, 1e-8, 1e-10)
+        assert np.array_equal(fl, fl_o)
+        assert np.abs(A - A_o).max() <= 1e-8 and np.abs(ov - ov_o).max() <= 1e-8 and np.abs(dr - dr_o).max() <= 1e-9
+    bad = ics.copy()
+    bad[2, 40] = np.nan
+    A2, ov2, dr2, fl2 = gpu_bs23(cfg, obs, bad, dt, n_steps, 1e-8, 1e-10, precision)
+    keep = np.arange(65) != 40
+    assert np.array_equal(A2[keep], A[keep]) and np.array_equal(ov2[keep], ov[keep])
+    assert np.array_equal(dr2[keep], dr[keep]) and np.array_equal(fl2[keep], fl[keep])
+    assert fl2[40] & 2
+
+
 def test_barred_model_windows(gpu):
     """Rotating Ferrers bar, 64 orbits x 300 steps on the barred model's grid
     (18,000 mass and 30,000 kinematic cells: 3 and 4 histogram windows)."""
