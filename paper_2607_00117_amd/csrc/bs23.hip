@@ -26,7 +26,8 @@
 //     evaluating the Jacobi drift (half of the orbits each, two steps of an orbit
 //     at a time), from states handed over in LDS, kRound attempts at a time.  Each lane's arithmetic is the same as in one wave.
 //     30,000 x 5,000 steps of the barred model in FP32: 107.5 ms in one wave with
-//     common steps, 46.7 now (54.9 with one drift wave).
+//     common steps, 44.9 now (54.9 with one drift wave, 46.7 without a raised
+//     priority for the integrating waves).
 //  2. k_hist_w: one workgroup per orbit (and window of columns when a row does
 //     not fit LDS): each event's weight dt_k / t_total is rounded to a 64-bit
 //     fixed-point integer in units of 2^-52 and added into an LDS histogram of
@@ -71,7 +72,7 @@ __device__ __forceinline__ void bs_rhs(const PotK& P, const double* y, double* f
 template <bool NB>
 __device__ __forceinline__ void bs_rhs(const PotK& P, const float* y, float* f, float& lamw) {
   float g[3], gb[3];
-  accel_f32<1, NB>(P, y[0], y[1], y[2], g[0], g[1], g[2], gb, lamw, 0);
+  accel_f32<1, NB, false>(P, y[0], y[1], y[2], g[0], g[1], g[2], gb, lamw, 0);
   const float W = (float)P.omega;
   f[0] = y[3] + W * y[1];
   f[1] = y[4] - W * y[0];
@@ -95,7 +96,7 @@ template <bool NB>
 __device__ __forceinline__ double bs_jacobi(const PotK& P, const float* y, float lamw) {
   double yd[6];
   for (int i = 0; i < 6; ++i) yd[i] = (double)y[i];
-  return jacobi_f64_drift<NB>(P, yd, lamw);
+  return jacobi_f64_drift<NB, false>(P, yd, lamw);
 }
 
 __device__ __forceinline__ double bs_pow(double e) { return pow(e, -1.0 / 3.0); }
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(kBsThreads) void k_bs23(PotK P, ObsK O, const doubl
   __shared__ float lam0[64];
   __shared__ int32_t badl[64];
   __shared__ int32_t last;  // the round after which every lane has its S steps (-1: not yet)
-  const int lane = threadIdx.x & 63, role = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // this lane's orbit; a drift wave's lanes l and l + 32 share one
   const int ol = role < 2 ? lane : 32 * (role - 2) + (lane & 31);
   const int64_t o = (int64_t)blockIdx.x * 64 + ol;
@@ -139,6 +140,7 @@ __global__ __launch_bounds__(kBsThreads) void k_bs23(PotK P, ObsK O, const doubl
   double tt = 0.0, dmax = 0.0, E0 = 0.0;
   bool bad = false;
   if (role == 0) {
+    __builtin_amdgcn_s_setprio(3);  // ahead of the other roles' waves on its SIMD
     bs_rhs<NB>(P, y, k1, lamw);
     lam0[lane] = lamw;
     if (lane == 0) last = -1;
@@ -202,17 +204,12 @@ __global__ __launch_bounds__(kBsThreads) void k_bs23(PotK P, ObsK O, const doubl
         for (int i = 0; i < 6; ++i)
           if (!isfinite(y[i])) bad = true;
         tt += (double)dt;
-        int mc[4], kc[4];
+        uint32_t mc[4], kc[4];
         cells4<T, CYL>(P, O, y, mc, kc);
-        uint64_t vm = 0, vk = 0;
-        for (int c = 0; c < 4; ++c) {
-          vm |= (uint64_t)(uint16_t)(mc[c] < 0 ? 0xFFFF : mc[c]) << (16 * c);
-          vk |= (uint64_t)(uint16_t)(kc[c] < 0 ? 0xFFFF : kc[c]) << (16 * c);
-        }
         if (mine) {
           const int64_t e = o * S + s;
-          ev_m[e] = vm;
-          ev_k[e] = vk;
+          ev_m[e] = pack4(mc);
+          ev_k[e] = pack4(kc);
           wts[e] = (double)dt;
         }
         ++s;

@@ -1,8 +1,8 @@
 // integrate_and_bin, bin_points, integrate_orbits and the histogram kernel.
 //
 // integrate_and_bin runs in two kernels per orbit chunk:
-//  1. k_integrate: one orbit per lane, packed cell indices of every step and
-//     mirror copy appended to each orbit's event stream (workspace);
+//  1. k_integrate / k_integrate_split: one orbit per lane, packed cell indices of
+//     every step and mirror copy appended to each orbit's event stream (workspace);
 //  2. k_hist: one workgroup per group of orbits per block; the orbit's row is
 //     an LDS-privatised histogram of 16-bit counters (two per 32-bit word,
 //     ds_add of 1 or 1<<16), filled from the event stream and written to the
@@ -153,11 +153,11 @@ __global__ void k_bin_points(const PotK P, ObsK O, const T* __restrict__ pts, in
   if (i >= n) return;
   T s[6];
   for (int k = 0; k < 6; ++k) s[k] = pts[(int64_t)k * n + i];
-  int mc[4], kc[4];
+  uint32_t mc[4], kc[4];
   cells4<T, CYL>(P, O, s, mc, kc);
   for (int c = 0; c < 4; ++c) {
-    mass[4 * i + c] = mc[c];
-    kin[4 * i + c] = kc[c];
+    mass[4 * i + c] = mc[c] == kNoCell ? -1 : (int32_t)mc[c];
+    kin[4 * i + c] = kc[c] == kNoCell ? -1 : (int32_t)kc[c];
   }
 }
 

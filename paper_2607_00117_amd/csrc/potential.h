@@ -17,6 +17,23 @@ namespace sw {
 __device__ __forceinline__ float rcpf_(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float rsqf_(float x) { return __builtin_amdgcn_rsqf(x); }
 
+// a b + c: fused (F) or rounded twice.  The single-precision force and its drift
+// check are compiled into several kernels that must agree on every bit (an orbit's
+// histogram does not survive a rounding difference), and which product of a b + c d
+// the compiler fuses changes with the code around it: contractions are written out.
+// F: the leapfrog integrator; the adaptive one runs without.
+template <bool F>
+__device__ __forceinline__ float mad_(float a, float b, float c) {
+#pragma clang fp contract(off)
+  return F ? __builtin_fmaf(a, b, c) : a * b + c;
+}
+template <bool F>
+__device__ __forceinline__ double mad_(double a, double b, double c) {
+#pragma clang fp contract(off)
+  return F ? __builtin_fma(a, b, c) : a * b + c;
+}
+__device__ __forceinline__ float logf_(float x) { return __logf(x); }
+
 // ---------------------------------------------------------------------------
 // Ferrers n = 2 bar.  With e_j = (a_j^2 + u) / K:
 //   int (1 - m^2)^2 du / ((a_i^2 + u) Delta) = K^-3/2 sum_n W_n (1 - m_n^2)^2 / (e_i sqrt(e_x e_y e_z))
@@ -35,26 +52,27 @@ constexpr int kNewtonWarm32 = 3;  // Newton steps from the previous step's lam
 // With LPO > 1 lanes per orbit, lane `part` of the group takes the nodes
 // n = part, part + LPO, ... and returns its share of the force (the shares
 // add up across the group); every lane computes lam.
-template <int LPO = 1>
+template <int LPO, bool F>
 __device__ __forceinline__ void ferrers_accel_f32(const CompK& C, const float* gq, const float* gw, float x,
                                                   float y, float z, float& gx, float& gy, float& gz,
                                                   float& lam_io, int part = 0) {
+#pragma clang fp contract(off)
   const float A0 = C.f[0], A1 = C.f[1], A2 = C.f[2], Amin = C.f[3], kF = C.f[4], Amax = C.f[6];
   const float x2 = x * x, y2 = y * y, z2 = z * z;
   const bool cold = lam_io < 0.0f;
-  float lam = cold ? fmaxf(0.0f, x2 + y2 + z2 - Amax) : lam_io;
+  float lam = cold ? fmaxf(0.0f, mad_<F>(z, z, mad_<F>(x, x, y2)) - Amax) : lam_io;
   const int n_it = cold ? kNewton32 : kNewtonWarm32;
   for (int it = 0; it < n_it; ++it) {
     float i0 = rcpf_(A0 + lam), i1 = rcpf_(A1 + lam), i2 = rcpf_(A2 + lam);
     float t0 = x2 * i0, t1 = y2 * i1, t2 = z2 * i2;
-    float f = (t0 + t1) + (t2 - 1.0f);
-    float fp = t0 * i0 + t1 * i1 + t2 * i2;
-    lam = fmaxf(0.0f, lam + f * rcpf_(fp));
+    float f = mad_<F>(x2, i0, t1) + mad_<F>(z2, i2, -1.0f);
+    float fp = mad_<F>(i2, t2, mad_<F>(i0, t0, i1 * t1));
+    lam = fmaxf(0.0f, mad_<F>(f, rcpf_(fp), lam));
   }
   lam_io = lam;
   const float K = Amin + lam;
   const float iK = rcpf_(K);
-  const float D0 = (A0 + lam) * iK, D1 = (A1 + lam) * iK, D2 = (A2 + lam) * iK;
+  const float B0 = A0 + lam, B1 = A1 + lam, B2 = A2 + lam;
   const float xs = x2 * iK, ys = y2 * iK, zs = z2 * iK;
   float F0 = 0.0f, F1 = 0.0f, F2 = 0.0f;
 #pragma unroll
@@ -65,33 +83,35 @@ __device__ __forceinline__ void ferrers_accel_f32(const CompK& C, const float* g
       q = part ? gq[m * LPO + 1] : q;
       W = part ? gw[m * LPO + 1] : W;
     }
-    float e0 = D0 + q, e1 = D1 + q, e2 = D2 + q;
+    float e0 = mad_<F>(B0, iK, q), e1 = mad_<F>(B1, iK, q), e2 = mad_<F>(B2, iK, q);
     float e12 = e1 * e2, e02 = e0 * e2, e01 = e0 * e1;
     float s = rsqf_(e0 * e12);
     float iP = s * s;
     float i0 = e12 * iP, i1 = e02 * iP, i2 = e01 * iP;
-    float w = fmaxf(1.0f - (xs * i0 + ys * i1 + zs * i2), 0.0f);
+    float w = fmaxf(1.0f - mad_<F>(zs, i2, mad_<F>(xs, i0, ys * i1)), 0.0f);
     float c = W * (w * w) * s;
-    F0 += c * i0;
-    F1 += c * i1;
-    F2 += c * i2;
+    F0 = mad_<F>(c, i0, F0);
+    F1 = mad_<F>(c, i1, F1);
+    F2 = mad_<F>(c, i2, F2);
   }
   const float sc = kF * iK * rsqf_(K);
-  gx -= sc * x * F0;
-  gy -= sc * y * F1;
-  gz -= sc * z * F2;
+  gx = mad_<F>(-(sc * x), F0, gx);
+  gy = mad_<F>(-(sc * y), F1, gy);
+  gz = mad_<F>(-(sc * z), F2, gz);
 }
 
 // lam by Newton from the left bracket, converged in double precision.
-__device__ __forceinline__ double ferrers_lambda_f64(const CompK& C, double x2, double y2, double z2) {
+template <bool F = false>
+__device__ __forceinline__ double ferrers_lambda_f64(const CompK& C, double x2, double y2, double z2, double r2) {
+#pragma clang fp contract(off)
   const double A0 = C.c[0], A1 = C.c[1], A2 = C.c[2], Amax = C.c[6];
-  double lam = fmax(0.0, x2 + y2 + z2 - Amax);
+  double lam = fmax(0.0, r2 - Amax);
   for (int it = 0; it < 60; ++it) {
     double i0 = 1.0 / (A0 + lam), i1 = 1.0 / (A1 + lam), i2 = 1.0 / (A2 + lam);
     double t0 = x2 * i0, t1 = y2 * i1, t2 = z2 * i2;
-    double f = t0 + t1 + t2 - 1.0;
+    double f = mad_<F>(z2, i2, mad_<F>(x2, i0, t1)) - 1.0;
     if (!(f > 0.0)) break;
-    double fp = t0 * i0 + t1 * i1 + t2 * i2;
+    double fp = mad_<F>(i2, t2, mad_<F>(i0, t0, i1 * t1));
     double nl = lam + f / fp;
     if (!(nl > lam)) break;
     lam = nl;
@@ -103,7 +123,7 @@ __device__ __forceinline__ double ferrers_lambda_f64(const CompK& C, double x2, 
 __device__ inline void ferrers_f64(const CompK& C, const double* gq, const double* gw, double x, double y,
                                    double z, double* phi, double* g) {
   const double x2 = x * x, y2 = y * y, z2 = z * z;
-  const double lam = ferrers_lambda_f64(C, x2, y2, z2);
+  const double lam = ferrers_lambda_f64(C, x2, y2, z2, x2 + y2 + z2);
   const double K = C.c[3] + lam;
   const double D0 = (C.c[0] + lam) / K, D1 = (C.c[1] + lam) / K, D2 = (C.c[2] + lam) / K;
   const double xs = x2 / K, ys = y2 / K, zs = z2 / K;
@@ -275,62 +295,67 @@ __device__ __forceinline__ void needle_bar(const T* K, const T* gq, const T* gw,
 // whole bar force and the caller adds it.  NB: the potential may hold needle
 // bars (their code is compiled in only then, so that it does not weigh on the
 // registers of the kernels that integrate other potentials).
-template <int LPO = 1, bool NB = false>
+template <int LPO, bool NB, bool F>
 __device__ __forceinline__ void accel_f32(const PotK& P, float x, float y, float z, float& gx, float& gy,
                                           float& gz, float* gb, float& lamw, int part = 0) {
+#pragma clang fp contract(off)
   gx = 0.0f; gy = 0.0f; gz = 0.0f;
   gb[0] = 0.0f; gb[1] = 0.0f; gb[2] = 0.0f;
+  const float y2 = y * y, z2 = z * z, R2 = mad_<F>(x, x, y2), r2 = mad_<F>(z, z, R2);
   const int nc = P.n_comp;
   bool first_bar = true;
   for (int i = 0; i < nc; ++i) {
     const CompK& C = P.comp[i];
     switch (C.kind) {
       case SW_KEPLER: {
-        float ir = rsqf_(x * x + y * y + z * z);
+        float ir = rsqf_(r2);
         float f = C.f[0] * ir * ir * ir;
-        gx -= f * x; gy -= f * y; gz -= f * z;
+        gx = mad_<F>(-f, x, gx); gy = mad_<F>(-f, y, gy); gz = mad_<F>(-f, z, gz);
         break;
       }
       case SW_ISOCHRONE: {
-        float r2 = x * x + y * y + z * z;
         float u = C.f[2] + r2;
         float iu = rsqf_(u);
-        float s = u * iu;
-        float den = C.f[1] + s;
+        float den = mad_<F>(u, iu, C.f[1]);
         float f = C.f[0] * rcpf_(den * den) * iu;
-        gx -= f * x; gy -= f * y; gz -= f * z;
+        gx = mad_<F>(-f, x, gx); gy = mad_<F>(-f, y, gy); gz = mad_<F>(-f, z, gz);
         break;
       }
       case SW_PLUMMER: {
-        float id = rsqf_(x * x + y * y + z * z + C.f[1]);
+        float id = rsqf_(r2 + C.f[1]);
         float f = C.f[0] * id * id * id;
-        gx -= f * x; gy -= f * y; gz -= f * z;
+        gx = mad_<F>(-f, x, gx); gy = mad_<F>(-f, y, gy); gz = mad_<F>(-f, z, gz);
         break;
       }
       case SW_MN: {
-        float zz = z * z + C.f[2];
+        float zz = z2 + C.f[2];
         float iz = rsqf_(zz);
-        float s = C.f[1] + zz * iz;
-        float iD = rsqf_(x * x + y * y + s * s);
+        float s = mad_<F>(zz, iz, C.f[1]);
+        float iD = rsqf_(mad_<F>(s, s, R2));
         float f = C.f[0] * iD * iD * iD;
-        gx -= f * x; gy -= f * y; gz -= f * z * s * iz;
+        gx = mad_<F>(-f, x, gx); gy = mad_<F>(-f, y, gy); gz = mad_<F>(-iz, f * z * s, gz);
         break;
       }
       case SW_NFW_Q: {
-        float m2 = x * x + y * y + z * z * C.f[2];
+        float m2 = mad_<F>(z2, C.f[2], R2);
         float im = rsqf_(m2);
         float xr = m2 * im * C.f[5];  // m / R_s
         // T(x) = ln(1+x)/x^2 - 1/(x(1+x)); dPhi/dm = G M_DM / R_s^2 * T(m / R_s)
         float T;
         if (xr < 0.1f) {
-          T = 0.5f + xr * (-2.0f / 3 + xr * (0.75f + xr * (-0.8f + xr * (5.0f / 6 + xr * (-6.0f / 7 +
-              xr * (0.875f + xr * (-8.0f / 9)))))));
+          T = mad_<F>(xr, -8.0f / 9, 0.875f);
+          T = mad_<F>(xr, T, -6.0f / 7);
+          T = mad_<F>(xr, T, 5.0f / 6);
+          T = mad_<F>(xr, T, -0.8f);
+          T = mad_<F>(xr, T, 0.75f);
+          T = mad_<F>(xr, T, -2.0f / 3);
+          T = mad_<F>(xr, T, 0.5f);
         } else {
           float ix = rcpf_(xr);
-          T = ix * (__logf(1.0f + xr) * ix - rcpf_(1.0f + xr));
+          T = ix * mad_<F>(logf_(1.0f + xr), ix, -rcpf_(1.0f + xr));
         }
         float f = (m2 > 0.0f) ? C.f[4] * T * im : 0.0f;
-        gx -= f * x; gy -= f * y; gz -= f * z * C.f[2];
+        gx = mad_<F>(-f, x, gx); gy = mad_<F>(-f, y, gy); gz = mad_<F>(-C.f[2], f * z, gz);
         break;
       }
       case SW_DA_T3:
@@ -344,11 +369,11 @@ __device__ __forceinline__ void accel_f32(const PotK& P, float x, float y, float
         break;
       case SW_FERRERS2:
         if (first_bar) {
-          ferrers_accel_f32<LPO>(C, P.gq32, P.gw32, x, y, z, gb[0], gb[1], gb[2], lamw, part);
+          ferrers_accel_f32<LPO, F>(C, P.gq32, P.gw32, x, y, z, gb[0], gb[1], gb[2], lamw, part);
           first_bar = false;
         } else {
           float cold = -1.0f;
-          ferrers_accel_f32<LPO>(C, P.gq32, P.gw32, x, y, z, gb[0], gb[1], gb[2], cold, part);
+          ferrers_accel_f32<LPO, F>(C, P.gq32, P.gw32, x, y, z, gb[0], gb[1], gb[2], cold, part);
         }
         break;
       default:
@@ -434,31 +459,33 @@ __device__ inline double needle_phi_f64(const PotK& P, const CompK& C, double x,
 }
 
 // Potential of one analytic (non-bar) component.
+template <bool F = false>
 __device__ inline double phi_analytic_f64(const CompK& C, double x, double y, double z) {
+#pragma clang fp contract(off)
   double v = 0.0;
   switch (C.kind) {
     case SW_KEPLER:
-      v = -C.c[0] / sqrt(x * x + y * y + z * z);
+      v = -C.c[0] / sqrt(mad_<F>(z, z, mad_<F>(x, x, y * y)));
       break;
     case SW_ISOCHRONE: {
-      double r2 = x * x + y * y + z * z;
+      double r2 = mad_<F>(z, z, mad_<F>(x, x, y * y));
       v = -C.c[0] / (C.c[1] + sqrt(C.c[2] + r2));
       break;
     }
     case SW_PLUMMER: {
-      double r2 = x * x + y * y + z * z;
+      double r2 = mad_<F>(z, z, mad_<F>(x, x, y * y));
       v = -C.c[0] / sqrt(r2 + C.c[1]);
       break;
     }
     case SW_MN: {
-      double R2 = x * x + y * y;
+      double R2 = mad_<F>(x, x, y * y);
       double zeta = sqrt(z * z + C.c[2]);
       double sm = C.c[1] + zeta;
-      v = -C.c[0] / sqrt(R2 + sm * sm);
+      v = -C.c[0] / sqrt(mad_<F>(sm, sm, R2));
       break;
     }
     case SW_NFW_Q: {
-      double m = sqrt(x * x + y * y + z * z / C.c[3]);
+      double m = sqrt(mad_<F>(x, x, y * y) + z * z / C.c[3]);
       v = (m == 0.0) ? -C.c[0] / C.c[1] : -C.c[0] * log1p(m / C.c[1]) / m;
       break;
     }
@@ -501,21 +528,25 @@ __device__ inline double jacobi_f64(const PotK& P, const double* s6) {
 // root refined by two Newton-Raphson steps; the analytic components are as
 // in phi_f64.  Its error against phi_f64 is far below the drift it checks.
 // ---------------------------------------------------------------------------
+template <bool F>
 __device__ __forceinline__ double rsq_f64(double v) {
+#pragma clang fp contract(off)
   double y = __builtin_amdgcn_rsq(v);
-  y = y * (1.5 - 0.5 * v * y * y);
-  y = y * (1.5 - 0.5 * v * y * y);
+  y = y * mad_<F>(-(0.5 * v * y), y, 1.5);
+  y = y * mad_<F>(-(0.5 * v * y), y, 1.5);
   return y;
 }
 
+template <bool F>
 __device__ inline double ferrers_phi_drift(const CompK& C, const float* gq, const float* gw, double x, double y,
                                            double z, double lam) {
+#pragma clang fp contract(off)
   const double x2 = x * x, y2 = y * y, z2 = z * z;
   for (int it = 0; it < 2; ++it) {
     const double i0 = 1.0 / (C.c[0] + lam), i1 = 1.0 / (C.c[1] + lam), i2 = 1.0 / (C.c[2] + lam);
     const double t0 = x2 * i0, t1 = y2 * i1, t2 = z2 * i2;
-    const double f = t0 + t1 + t2 - 1.0;
-    const double fp = t0 * i0 + t1 * i1 + t2 * i2;
+    const double f = mad_<F>(z2, i2, mad_<F>(x2, i0, t1)) - 1.0;
+    const double fp = mad_<F>(i2, t2, mad_<F>(i0, t0, i1 * t1));
     lam = fmax(0.0, lam + f / fp);
   }
   const double K = C.c[3] + lam, iK = 1.0 / K;
@@ -526,16 +557,20 @@ __device__ inline double ferrers_phi_drift(const CompK& C, const float* gq, cons
     const double q = (double)gq[n], W = (double)gw[n];
     const double e0 = D0 + q, e1 = D1 + q, e2 = D2 + q;
     const double e12 = e1 * e2;
-    const double sv = rsq_f64(e0 * e12);
+    const double sv = rsq_f64<F>(e0 * e12);
     const double iP = sv * sv;
-    const double w = fmax(1.0 - (xs * e12 + ys * e0 * e2 + zs * e0 * e1) * iP, 0.0);
-    Fp += W * (w * w * w) * sv;
+    const double m2 = mad_<F>(zs * e0, e1, mad_<F>(xs, e12, ys * e0 * e2));
+    const double w = fmax(mad_<F>(-m2, iP, 1.0), 0.0);
+    Fp = mad_<F>(W * (w * w * w), sv, Fp);
   }
-  return -C.c[5] * Fp * rsq_f64(K);
+  return -C.c[5] * Fp * rsq_f64<F>(K);
 }
 
-template <bool NB = false>
+// F: with fused multiply-adds (the leapfrog integrator), or without (the
+// adaptive one)
+template <bool NB = false, bool F = true>
 __device__ inline double jacobi_f64_drift(const PotK& P, const double* s6, float lamw) {
+#pragma clang fp contract(off)
   const double x = s6[0], y = s6[1], z = s6[2];
   double phi = 0.0;
   bool first_bar = true;
@@ -543,20 +578,20 @@ __device__ inline double jacobi_f64_drift(const PotK& P, const double* s6, float
     const CompK& C = P.comp[i];
     double v;
     if (C.kind == SW_FERRERS2) {
-      const double lam = (first_bar && lamw >= 0.0f) ? (double)lamw : ferrers_lambda_f64(C, x * x, y * y, z * z);
+      const double lam = (first_bar && lamw >= 0.0f) ? (double)lamw : ferrers_lambda_f64<F>(C, x * x, y * y, z * z, mad_<F>(z, z, mad_<F>(x, x, y * y)));
       first_bar = false;
-      v = ferrers_phi_drift(C, P.gq32, P.gw32, x, y, z, lam);
+      v = ferrers_phi_drift<F>(C, P.gq32, P.gw32, x, y, z, lam);
     } else if (C.kind == SW_DA_T3 || C.kind == SW_DA_V4) {
       v = 0.0;
       if constexpr (NB) v = needle_phi_f64(P, C, x, y, z);
     } else {
-      v = phi_analytic_f64(C, x, y, z);
+      v = phi_analytic_f64<F>(C, x, y, z);
     }
     phi = phi + v;
   }
-  const double kin = 0.5 * (s6[3] * s6[3] + s6[4] * s6[4] + s6[5] * s6[5]);
-  const double Lz = s6[0] * s6[4] - s6[1] * s6[3];
-  return kin + phi - P.omega * Lz;
+  const double p2 = mad_<F>(s6[5], s6[5], mad_<F>(s6[3], s6[3], s6[4] * s6[4]));
+  const double Lz = mad_<F>(s6[0], s6[4], -(s6[1] * s6[3]));
+  return mad_<F>(-P.omega, Lz, mad_<F>(0.5, p2, phi));
 }
 
 // ---------------------------------------------------------------------------
@@ -658,23 +693,41 @@ __device__ __forceinline__ T proj3(T r0, T r1, T r2, T a, T b, T c) {
   return r0 * a + r1 * b + r2 * c;
 }
 
-// Cells of the four mirror copies (Table 1) of one bar-frame state.
-// Copies: 0 (x,y,z), 1 (x,y,-z), 2 (-x,-y,z), 3 (-x,-y,-z), applied to
-// position and velocity alike.  Projections of copies 2 and 3 are exactly
-// the negations of copies 1 and 0 (IEEE rounding is sign-symmetric).
-// mcell/kcell: -1 when outside the block.
+// Index of v among n cells; outside, some value that is no cell when read as
+// unsigned.  Single precision: floor by the conversion itself, a NaN below the
+// first cell by the maximum (which returns its other operand).
+__device__ __forceinline__ int bin_any(float v, float lo, float inv, int) {
+#pragma clang fp contract(off)
+  const float t = fmaxf((v - lo) * inv, -1.0f);
+  int i;
+  asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(t));
+  return i;
+}
+__device__ __forceinline__ int bin_any(double v, double lo, double inv, int n) { return bin1<double>(v, lo, inv, n); }
+
+constexpr uint32_t kNoCell = 0xFFFFu;  // outside the block (blocks hold fewer cells)
+
+// Cells of the four mirror copies (Table 1) of one bar-frame state, kNoCell
+// when outside the block.  Copies: 0 (x,y,z), 1 (x,y,-z), 2 (-x,-y,z),
+// 3 (-x,-y,-z), applied to position and velocity alike.  Projections of copies
+// 2 and 3 are exactly the negations of copies 1 and 0 (IEEE rounding is
+// sign-symmetric).  No branches: the four aperture loads are in flight together,
+// from pixel 0 for a copy outside the field of view.  With a branch and a wait for
+// each copy a leapfrog launch in one wave per tile took 6.6 ms (8,000 FP32 orbits of
+// the barred model x 2,000 steps) and 2.3 ms (2,000 FP64 x 1,000); 5.3 and 2.0 now.
 // CYL: the mass grid is cylindrical (compiled in only for such grids: the
 // sector tables are indexed at run time, which would weigh on the registers of
 // the Cartesian kernels)
 template <typename T, bool CYL = false>
-__device__ __forceinline__ void cells4(const PotK& P, const ObsK& O, const T* s6, int* mcell, int* kcell) {
+__device__ __forceinline__ void cells4(const PotK& P, const ObsK& O, const T* s6, uint32_t* mcell, uint32_t* kcell) {
   using Q = ObsT<T>;
   const T x = s6[0], y = s6[1], z = s6[2], px = s6[3], py = s6[4], pz = s6[5];
-  const int ixp = bin1<T>(x, Q::lo(O, 0), Q::inv(O, 0), O.nx), ixm = bin1<T>(-x, Q::lo(O, 0), Q::inv(O, 0), O.nx);
-  const int iyp = bin1<T>(y, Q::lo(O, 1), Q::inv(O, 1), O.ny), iym = bin1<T>(-y, Q::lo(O, 1), Q::inv(O, 1), O.ny);
-  const int izp = bin1<T>(z, Q::lo(O, 2), Q::inv(O, 2), O.nz), izm = bin1<T>(-z, Q::lo(O, 2), Q::inv(O, 2), O.nz);
-  int ixs[4] = {ixp, ixp, ixm, ixm}, iys[4] = {iyp, iyp, iym, iym};
-  const int izs[4] = {izp, izm, izp, izm};
+  const uint32_t nz = (uint32_t)O.nz, nyz = (uint32_t)O.ny * nz;
+  // an axis's share of the cell number; shares that hold a 0x10000 add up to no cell
+  const auto share = [](int i, int n, uint32_t stride) {
+    return (uint32_t)i < (uint32_t)n ? (uint32_t)i * stride : 0x10000u;
+  };
+  uint32_t xs[2], ys[2], zs[2];  // of the coordinate and of its negation
   if constexpr (CYL) {
     // (R, phi, z): R is the same for the four copies, the sector of (-x, -y) is that of the opposite point
     T R2;
@@ -682,17 +735,22 @@ __device__ __forceinline__ void cells4(const PotK& P, const ObsK& O, const T* s6
 #pragma clang fp contract(off)
       R2 = x * x + y * y;
     }
-    const int ir = cyl_rbin<T>(R2, Q::lo(O, 0), Q::rw(O), Q::inv(O, 0), O.nx);
-    const int sp = cyl_sector<T>(x, y, Q::sc(O), Q::ss(O), O.ny), sm = cyl_sector<T>(-x, -y, Q::sc(O), Q::ss(O), O.ny);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      ixs[c] = ir;
-      iys[c] = c < 2 ? sp : sm;
-    }
+    xs[0] = xs[1] = share(cyl_rbin<T>(R2, Q::lo(O, 0), Q::rw(O), Q::inv(O, 0), O.nx), O.nx, nyz);
+    ys[0] = share(cyl_sector<T>(x, y, Q::sc(O), Q::ss(O), O.ny), O.ny, nz);
+    ys[1] = share(cyl_sector<T>(-x, -y, Q::sc(O), Q::ss(O), O.ny), O.ny, nz);
+  } else {
+    xs[0] = share(bin_any(x, Q::lo(O, 0), Q::inv(O, 0), O.nx), O.nx, nyz);
+    xs[1] = share(bin_any(-x, Q::lo(O, 0), Q::inv(O, 0), O.nx), O.nx, nyz);
+    ys[0] = share(bin_any(y, Q::lo(O, 1), Q::inv(O, 1), O.ny), O.ny, nz);
+    ys[1] = share(bin_any(-y, Q::lo(O, 1), Q::inv(O, 1), O.ny), O.ny, nz);
   }
+  zs[0] = share(bin_any(z, Q::lo(O, 2), Q::inv(O, 2), O.nz), O.nz, 1u);
+  zs[1] = share(bin_any(-z, Q::lo(O, 2), Q::inv(O, 2), O.nz), O.nz, 1u);
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
-    mcell[c] = (ixs[c] < 0 || iys[c] < 0 || izs[c] < 0) ? -1 : (ixs[c] * O.ny + iys[c]) * O.nz + izs[c];
+  for (int c = 0; c < 4; ++c) {
+    const uint32_t m = xs[c >> 1] + ys[c >> 1] + zs[c & 1];
+    mcell[c] = m < kNoCell ? m : kNoCell;
+  }
   const T X0 = proj3<T>(Q::R(P, 0), Q::R(P, 1), Q::R(P, 2), x, y, z);
   const T Y0 = proj3<T>(Q::R(P, 3), Q::R(P, 4), Q::R(P, 5), x, y, z);
   const T V0 = proj3<T>(Q::R(P, 6), Q::R(P, 7), Q::R(P, 8), px, py, pz);
@@ -700,20 +758,34 @@ __device__ __forceinline__ void cells4(const PotK& P, const ObsK& O, const T* s6
   const T Y1 = proj3<T>(Q::R(P, 3), Q::R(P, 4), Q::R(P, 5), x, y, -z);
   const T V1 = proj3<T>(Q::R(P, 6), Q::R(P, 7), Q::R(P, 8), px, py, -pz);
   const T Xs[4] = {X0, X1, -X1, -X0}, Ys[4] = {Y0, Y1, -Y1, -Y0}, Vs[4] = {V0, V1, -V1, -V0};
+  int ap[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
-    int jx = bin1<T>(Xs[c], Q::plo(O, 0), Q::pinv(O, 0), O.npx);
-    int jy = bin1<T>(Ys[c], Q::plo(O, 1), Q::pinv(O, 1), O.npy);
-    int kv = bin1<T>(Vs[c], Q::vlo(O), Q::vinv(O), O.nv);
-    int ap = -1;
-    if (jx >= 0 && jy >= 0) {
-      int pix = jx * O.npy + jy;
-      ap = O.pix2ap ? O.pix2ap[pix] : pix;
-    }
+    const int jx = bin_any(Xs[c], Q::plo(O, 0), Q::pinv(O, 0), O.npx);
+    const int jy = bin_any(Ys[c], Q::plo(O, 1), Q::pinv(O, 1), O.npy);
+    ap[c] = ((uint32_t)jx < (uint32_t)O.npx) & ((uint32_t)jy < (uint32_t)O.npy) ? jx * O.npy + jy : -1;
+  }
+  if (O.pix2ap) {
+    int at[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) at[c] = O.pix2ap[ap[c] < 0 ? 0 : ap[c]];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) ap[c] = ap[c] < 0 ? -1 : at[c];
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int kv = bin_any(Vs[c], Q::vlo(O), Q::vinv(O), O.nv);
     // with the surface block on, an event in an aperture outside the velocity
     // range keeps its aperture as code n_kin + ap (counted by that block only)
-    kcell[c] = ap < 0 ? -1 : (kv >= 0 ? ap * O.nv + kv : (O.surface ? O.n_kin + ap : -1));
+    const uint32_t out = O.surface ? (uint32_t)(O.n_kin + ap[c]) : kNoCell;
+    const uint32_t k = (uint32_t)kv < (uint32_t)O.nv ? (uint32_t)(ap[c] * O.nv + kv) : out;
+    kcell[c] = ap[c] < 0 ? kNoCell : k;
   }
+}
+
+// event word of four cells
+__device__ __forceinline__ uint64_t pack4(const uint32_t* c) {
+  return (uint64_t)(c[0] | c[1] << 16) | (uint64_t)(c[2] | c[3] << 16) << 32;
 }
 
 }  // namespace sw

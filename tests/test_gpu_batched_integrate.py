@@ -252,3 +252,31 @@ def test_pix2ap_batched_fp64_identical(gpu, surface):
         assert np.array_equal(ov[a:b], ov_o / (4.0 * n_steps)), k
         assert np.array_equal(dr[a:b], dr_o) and np.array_equal(fl[a:b], fl_o), k
     assert ov[:, 1].max() > 0  # unused pixels and the velocity range leave events out
+
+
+# orbit counts: less than a tile, its edges, more tiles than three waves share (512), ragged potentials in tiles of
+# their own (4 n_pot <= tiles; one empty, two smaller than a tile, chunk bounds inside); steps: around a hand-over (4)
+# and a stage (8, 16)
+@pytest.mark.parametrize("offsets,n_steps,every,ws", [
+    ([0, 1], 1, 1, None), ([0, 63], 3, 0, None), ([0, 64], 5, 2, None), ([0, 130], 33, 3, None),
+    ([0, 33000], 17, 4, None), ([0, 700, 700, 735, 1600, 1663], 18, 1, None),
+    ([0, 700, 700, 735, 1600, 1663], 18, 1, 1000), ([0, 20011, 33100], 9, 5, None)])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_waves_sharing_a_tile_give_the_bits_of_one_wave(gpu, offsets, n_steps, every, ws, dtype):
+    P = lib()
+    ics, dt = _ics(offsets[-1], seed=7)
+    ics[:, 0] = 0.0  # the force of a point mass at its centre: NaN energies and states
+    fams = FP64_POTS[3:] + [([("mn", (4e10, 3.0, 0.3)), ("ferrers2", (1e10, 4.0, 1.5, 1.0))], (0.3, 0.9, 0.1))]
+    pots = [P.build_potential(c, 40.0 * (i % 2), e) for i, (c, e) in enumerate((fams * 3)[:len(offsets) - 1])]
+    obs = dict(W.SMALL["obs"], drift_every=every)
+    got = _gpu_batched(pots, offsets, ics, dt, n_steps, obs, dtype, ws)
+    with _Tuning(integrate_waves_per_cu=8):
+        ref = _gpu_batched(pots, offsets, ics, dt, n_steps, obs, dtype, ws)
+    for g, r in zip(got, ref):
+        assert g.tobytes() == r.tobytes()
+    for k, pot in enumerate(pots):  # and of each potential alone
+        a, b = offsets[k], offsets[k + 1]
+        if a < b:
+            alone = _gpu_batched([pot], [0, b - a], ics[:, a:b], dt[a:b], n_steps, obs, dtype)
+            for g, r in zip(got, alone):
+                assert g[a:b].tobytes() == r.tobytes()
