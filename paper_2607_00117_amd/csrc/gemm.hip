@@ -788,17 +788,26 @@ __global__ __launch_bounds__(kThreads) void k_trmv(const float* __restrict__ S, 
 // every wave) and streams their columns 256 at a time, four per lane: one load
 // of x serves up to 16 rows.  A chunk that straddles the diagonal of a group
 // of rows is masked entry by entry; a chunk outside a group's half is skipped.
-template <bool LOWER>
-__global__ __launch_bounds__(kThreads) void k_trmv16(const float* __restrict__ S, int64_t n, int64_t ld, int64_t sK,
-                                                     const float* __restrict__ x, float* __restrict__ y, int64_t sv,
-                                                     const double* __restrict__ act, int act_stride) {
+//
+// Bound by the stream of S: 64 matrices of 1,792 columns at 6.5 TB/s (four waves
+// a workgroup, loads that do not stay in the caches).  A launch of few waves is
+// bound by the latency of its chunks instead (SMALL): a wave per workgroup, the
+// next chunk's loads in flight, and cached loads, since S then often fits the L2s
+// from one iteration to the next: one matrix of 1,792 columns 14.1 -> 10.6 us.  Up to
+// kTrmvSmall waves, one per SIMD; from about 200 on the two take the same time.
+constexpr int64_t kTrmvSmall = 1024;
+template <bool LOWER, bool SMALL>
+__global__ __launch_bounds__(SMALL ? 64 : kThreads) void k_trmv16(const float* __restrict__ S, int64_t n, int64_t ld,
+                                                                  int64_t sK, const float* __restrict__ x,
+                                                                  float* __restrict__ y, int64_t sv,
+                                                                  const double* __restrict__ act, int act_stride) {
   const int64_t b = blockIdx.y;
   if (act && act[b * act_stride] == 0.0) return;
   S += b * sK;
   x += b * sv;
   y += b * sv;
   const int lane = threadIdx.x & 63;
-  const int64_t g = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  const int64_t g = SMALL ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   if (g >= n / 16) return;
   const int64_t R[2] = {8 * g, n - 8 - 8 * g};  // first rows of the two groups
   // the columns that a row of either group holds
@@ -808,30 +817,33 @@ __global__ __launch_bounds__(kThreads) void k_trmv16(const float* __restrict__ S
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int r = 0; r < 8; ++r) acc[h][r] = 0.0f;
-  for (int64_t jb = lo; jb < hi; jb += 256) {
+  struct Chunk {
+    f32x4 sr[2][8], xv;
+  };
+  const auto used = [&](int h, int64_t jb) { return LOWER ? jb <= R[h] + 7 : jb + 255 >= R[h]; };
+  const auto load = [&](int64_t jb, Chunk& c) {
     const int64_t j = jb + 4 * lane;
     const bool in = j < n;
-    bool use[2], full[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      use[h] = LOWER ? jb <= R[h] + 7 : jb + 255 >= R[h];
-      full[h] = LOWER ? jb + 255 <= R[h] : jb >= R[h] + 7;
-    }
-    f32x4 sr[2][8];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int r = 0; r < 8; ++r)
-        sr[h][r] = use[h] && in ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(S + (R[h] + r) * ld + j))
-                                : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const f32x4 xv = in ? *reinterpret_cast<const f32x4*>(x + j) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int r = 0; r < 8; ++r) {
+        const f32x4* p = reinterpret_cast<const f32x4*>(S + (R[h] + r) * ld + j);
+        c.sr[h][r] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (used(h, jb) && in) c.sr[h][r] = SMALL ? *p : __builtin_nontemporal_load(p);
+      }
+    c.xv = in ? *reinterpret_cast<const f32x4*>(x + j) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  };
+  const auto add = [&](int64_t jb, const Chunk& c) {
+    const int64_t j = jb + 4 * lane;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      if (!use[h]) continue;
-      if (full[h]) {
+      if (!used(h, jb)) continue;
+      if (LOWER ? jb + 255 <= R[h] : jb >= R[h] + 7) {
 #pragma unroll
         for (int r = 0; r < 8; ++r)
-          acc[h][r] += sr[h][r][0] * xv[0] + sr[h][r][1] * xv[1] + sr[h][r][2] * xv[2] + sr[h][r][3] * xv[3];
+          acc[h][r] += c.sr[h][r][0] * c.xv[0] + c.sr[h][r][1] * c.xv[1] + c.sr[h][r][2] * c.xv[2] +
+                       c.sr[h][r][3] * c.xv[3];
       } else {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
@@ -839,10 +851,27 @@ __global__ __launch_bounds__(kThreads) void k_trmv16(const float* __restrict__ S
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const bool ok = LOWER ? j + q <= row : j + q >= row;
-            acc[h][r] += ok ? sr[h][r][q] * xv[q] : 0.0f;
+            acc[h][r] += ok ? c.sr[h][r][q] * c.xv[q] : 0.0f;
           }
         }
       }
+    }
+  };
+  if constexpr (SMALL) {
+    Chunk c0, c1;
+    load(lo, c0);
+    for (int64_t jb = lo; jb < hi; jb += 512) {
+      if (jb + 256 < hi) load(jb + 256, c1);
+      add(jb, c0);
+      if (jb + 256 >= hi) break;
+      if (jb + 512 < hi) load(jb + 512, c0);
+      add(jb + 256, c1);
+    }
+  } else {
+    for (int64_t jb = lo; jb < hi; jb += 256) {
+      Chunk c;
+      load(jb, c);
+      add(jb, c);
     }
   }
 #pragma unroll
@@ -1212,11 +1241,19 @@ hipError_t inv_apply_rhs(const float* S, int64_t n, int64_t ld, int P, const flo
 hipError_t inv_apply(const float* S, int64_t n, int64_t ld, int64_t sK, int nb_prob, const float* r, float* tmp,
                      float* s, int64_t sv, const double* act, int act_stride, hipStream_t st) {
   if (n % 16 == 0 && g_trmv_rows == 16) {
-    const unsigned g = (unsigned)((n / 16 + kThreads / 64 - 1) / (kThreads / 64));
-    hipLaunchKernelGGL(k_trmv16<true>, dim3(g, (unsigned)nb_prob), dim3(kThreads), 0, st, S, n, ld, sK, r, tmp, sv,
-                       act, act_stride);
-    hipLaunchKernelGGL(k_trmv16<false>, dim3(g, (unsigned)nb_prob), dim3(kThreads), 0, st, S, n, ld, sK, tmp, s, sv,
-                       act, act_stride);
+    const bool small = n / 16 * nb_prob <= kTrmvSmall;
+    const unsigned g = (unsigned)(small ? n / 16 : (n / 16 + kThreads / 64 - 1) / (kThreads / 64));
+    const auto go = [&](auto kernel, const float* in, float* out) {
+      hipLaunchKernelGGL(kernel, dim3(g, (unsigned)nb_prob), dim3(small ? 64 : kThreads), 0, st, S, n, ld, sK, in, out,
+                         sv, act, act_stride);
+    };
+    if (small) {
+      go(k_trmv16<true, true>, r, tmp);
+      go(k_trmv16<false, true>, tmp, s);
+    } else {
+      go(k_trmv16<true, false>, r, tmp);
+      go(k_trmv16<false, false>, tmp, s);
+    }
     return hipGetLastError();
   }
   const unsigned g = (unsigned)((n / 2 + kThreads / 64 - 1) / (kThreads / 64));

@@ -278,6 +278,38 @@ def test_many_small_problems_equal_the_large_workgroups(gpu, dtype, quantum):
         assert kkt <= 1.5 * max(out[0][1][k].kkt, 1e-7)
 
 
+@pytest.mark.parametrize("together", [True, False])
+def test_history_passes_at_their_block_edges(gpu, together):
+    """Problems of 8 to 2,049 orbits (edges of the acceleration's 256-thread and 1,024-orbit blocks), each alone (fewer
+    blocks than CUs: the history's slots shared out) or as the first of 130 (more blocks, and more triangle waves than
+    SIMDs): the weights meet the KKT conditions of the oracle either way."""
+    import torch
+    P = lib()
+    rng = np.random.default_rng(29)
+    c, edges = 70, [8, 255, 256, 257, 1023, 1024, 1025, 2049]
+    sizes = edges + [12] * 122
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    A = np.where(rng.random((off[-1], c)) < 0.28, rng.integers(1, 300, size=(off[-1], c)), 0) / 4000.0
+    ds = np.stack([A[off[k]:off[k + 1]].T @ rng.exponential(1.0, sizes[k]) for k in range(len(sizes))])
+    ds = np.maximum(ds, 1e-3) * (1 + 0.02 * rng.normal(size=ds.shape))
+    sig = 0.02 * ds
+    for k0, k1 in [(0, len(sizes))] if together else [(k, k + 1) for k in range(len(edges))]:
+        sub = off[k0:k1 + 1] - off[k0]
+        opts = P._lib.SolveOpts()
+        opts.gram, opts.nu, opts.refine_iter = 1, 1e-2, 200
+        w = torch.empty(int(sub[-1]), dtype=torch.float64, device=gpu)
+        ws = torch.full((P.solve_batched_workspace_bytes(sub, c, opts),), 255, dtype=torch.uint8, device=gpu)
+        _, reps = P.solve_weights_batched(torch.from_numpy(A[off[k0]:off[k1]]).to(gpu), sub,
+                                          torch.from_numpy(ds[k0:k1]).to(gpu), torch.from_numpy(sig[k0:k1]).to(gpu),
+                                          [1.0] * (k1 - k0), -1.0, opts, w, ws)
+        w = w.cpu().numpy()
+        for k in range(k0, min(k1, len(edges))):
+            U, y = N.scale_problem(A[off[k]:off[k + 1]], ds[k], sig[k], 1.0)
+            wk = w[off[k] - off[k0]:off[k + 1] - off[k0]]
+            kkt = N.kkt_residual(U, y, reps[k - k0].mu, wk) / np.abs(U.T @ y).max()
+            assert kkt <= 1.5 * max(reps[k - k0].kkt, 1e-7)
+
+
 def test_solve_dense_matrix_path(gpu):
     """A fully dense matrix takes the uncompressed passes over A."""
     rng = np.random.default_rng(12)
