@@ -101,3 +101,51 @@ def test_gh_fit_end_to_end(gpu, dtype):
     assert st == 0 or (st == -4 and rep.kkt < 1e-6)
     assert l1 < 1e-2
     assert abs(x_g / x_o - 1) < 1e-3
+
+
+# rows, apertures and bins around the 16 x 16 x 16 tile of the fit's kernel
+@pytest.mark.parametrize("n,n_ap,nv,n_gh", [(1, 1, 1, 1), (15, 17, 16, 8), (16, 16, 17, 4), (33, 15, 33, 3), (17, 31, 30, 4)])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_fit_block_equals_the_moments(gpu, n, n_ap, nv, n_gh, dtype):
+    """The Gauss-Hermite columns of the fit matrix are the moments over gamma, to the bit (both sum the bins in order),
+    also with empty bins, infinities and NaN in the rows; the other columns are copies."""
+    import torch
+    P = lib()
+    rng = np.random.default_rng(n + nv)
+    td = torch.float64 if dtype == "f64" else torch.float32
+    n_mass, kin0 = 3, 3
+    surf0 = kin0 + n_ap * nv
+    A = np.where(rng.random((n, surf0 + n_ap)) < 0.4, rng.random((n, surf0 + n_ap)), 0.0)
+    if n > 1:
+        A[0, kin0], A[1, kin0 + n_ap * nv - 1] = np.inf, np.nan
+    At = torch.from_numpy(A).to(gpu, td)
+    v0, s, gamma = rng.normal(0, 50, n_ap), rng.uniform(50, 200, n_ap), rng.uniform(0.5, 2, n_ap)
+    mom = torch.empty((n, n_ap, n_gh + 1), dtype=torch.float64, device=gpu)
+    P.gh_moments(At, kin0, n_ap, nv, -450.0, 450.0, v0, s, mom,
+                 torch.empty(P.gh_workspace_bytes(n_ap, nv, n_gh), dtype=torch.uint8, device=gpu), n_gh)
+    F = torch.empty((n, n_mass + n_ap * (1 + n_gh)), dtype=td, device=gpu)
+    P.gh_fit_matrix(At, n_mass, kin0, surf0, n_ap, nv, -450.0, 450.0, v0, s, gamma, F,
+                    torch.empty(P.gh_fit_workspace_bytes(n_ap, nv, n_gh), dtype=torch.uint8, device=gpu), n_gh)
+    F, At = F.cpu().numpy(), At.cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        want = (mom.cpu().numpy()[:, :, 1:] * (1.0 / gamma)[None, :, None]).transpose(0, 2, 1).reshape(n, -1)
+    assert np.array_equal(F[:, n_mass + n_ap:], want.astype(F.dtype), equal_nan=True)
+    assert np.array_equal(F[:, :n_mass], At[:, :n_mass], equal_nan=True)
+    assert np.array_equal(F[:, n_mass:n_mass + n_ap], At[:, surf0:], equal_nan=True)
+
+
+# columns around the 256-thread and 1,024-entry steps of the bundling kernel, rows per bundle around its four loads
+@pytest.mark.parametrize("nb,c,nd", [(1, 1, 1), (3, 255, 2), (7, 256, 3), (5, 257, 4), (300, 7, 5), (2, 1025, 8), (3, 3001, 9)])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_bundle_rows_edges(gpu, nb, c, nd, dtype):
+    import torch
+    P = lib()
+    rng = np.random.default_rng(c)
+    A = rng.normal(size=(nb * nd, c)).astype(np.float64 if dtype == "f64" else np.float32)
+    A[-1, -1] = -np.inf
+    out = torch.empty((nb, c), dtype=torch.from_numpy(A).dtype, device=gpu)
+    P.bundle_rows(torch.from_numpy(A).to(gpu), nd, out)
+    want = A[0::nd].astype(np.float64)
+    for k in range(1, nd):
+        want = want + A[k::nd]
+    assert np.array_equal(out.cpu().numpy(), (want / nd).astype(A.dtype))
