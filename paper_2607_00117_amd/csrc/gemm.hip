@@ -988,8 +988,16 @@ __global__ __launch_bounds__(256) void k_trmm_sum(const float* __restrict__ part
                                                   int64_t sv, float* __restrict__ Y) {
   const int64_t b = blockIdx.y, i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
+  part += b * sv + i;
   float t = 0.0f;
-  for (int z = 0; z < nzc; ++z) t += part[z * sz + b * sv + i];
+  for (int z0 = 0; z0 < nzc; z0 += 8) {  // eight loads in flight
+    float v[8];
+#pragma unroll
+    for (int z = 0; z < 8; ++z) v[z] = z0 + z < nzc ? part[(z0 + z) * sz] : 0.0f;
+#pragma unroll
+    for (int z = 0; z < 8; ++z)
+      if (z0 + z < nzc) t += v[z];
+  }
   Y[b * sv + i] = t;
 }
 

@@ -34,6 +34,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "gemm.h"
@@ -181,9 +182,13 @@ __global__ __launch_bounds__(256) void k_prep_xb(const TA* __restrict__ A, int64
 // Used when the matrix is dense enough that streaming it once per pass for all
 // right-hand sides beats the compressed passes, which read it once per group of
 // a few (the fit matrices with Gauss-Hermite blocks).  A 256-thread workgroup
-// owns a 128 x 64 output tile (vectors x outputs; four waves of 64 x 32 = 4 x 2
-// MFMA blocks of 16 x 16, so the matrix is read once per pass for up to 128
-// vectors) and one chunk of K.  Both operands are staged through LDS 16 at a
+// owns a 16 MB x 64 output tile (vectors x outputs; four waves of MB MFMA blocks
+// of 16 x 16, MB up to 8, so the matrix is read once per pass for up to 128
+// vectors) and one chunk of K.  The passes are bound by the matrix cores, and
+// rows of a tile that hold no vector are work for nothing, so MB follows the
+// number of vectors: a pair of passes over 7,500 x 3,655 entries in FP64 takes 298 us
+// for 100 vectors in tiles of 128, 275 in tiles of 112; a bootstrap of 30
+// vectors 115 ms in tiles of 128, 74 in tiles of 32; of 9, 97 and 54.  Both operands are staged through LDS 16 at a
 // time as [row][k] tiles whose rows are padded to 17 doubles, so that the
 // MFMA operand reads (16 rows at one k per quarter-wave) and the staging
 // writes fall in distinct banks; consecutive lanes load consecutive addresses
@@ -194,35 +199,32 @@ __global__ __launch_bounds__(256) void k_prep_xb(const TA* __restrict__ A, int64
 // compressed passes.
 // ---------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-constexpr int kDM = 128, kDN = 64, kDK = 16;
+constexpr int kDM = 128, kDN = 64, kDK = 16;  // kDM: the largest tile
 constexpr int kDKP = kDK + 1;
 
-template <typename TV, typename TA, bool TRANSB>
+template <typename TV, typename TA, bool TRANSB, int MB>
 __global__ __launch_bounds__(256) void k_dgemm_rhs(int64_t M, int64_t Nn, int64_t K, const TV* __restrict__ V,
                                                    int64_t ldv, const TA* __restrict__ A, int64_t lda, int64_t kc,
                                                    double* __restrict__ out, int64_t ldo, int64_t so) {
-  __shared__ double Vs[2][kDM][kDKP];  // [m][k]
+  __shared__ double Vs[2][16 * MB][kDKP];  // [m][k]
   __shared__ double Bs[2][kDN][kDKP];  // [n][k]
-  const int64_t m0 = (int64_t)blockIdx.y * kDM, n0 = (int64_t)blockIdx.x * kDN;
+  const int64_t m0 = (int64_t)blockIdx.y * (16 * MB), n0 = (int64_t)blockIdx.x * kDN;
   const int64_t k_beg = (int64_t)blockIdx.z * kc;
   const int64_t k_end = k_beg + kc < K ? k_beg + kc : K;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = w >> 1, wn = w & 1;
-  f64x4 acc[4][2];
+  f64x4 acc[MB];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int a = 0; a < MB; ++a) acc[a] = f64x4{0.0, 0.0, 0.0, 0.0};
   // staging: element e = tid + 256 q of the V tile is row e / 16, k e % 16; of the
   // A tile, TRANSB (A[n][k]) row n = e / 16, k e % 16, else (A[k][n]) k = e / 64,
   // n = e % 64: consecutive lanes read consecutive addresses
   const int64_t vrow = m0 + (tid >> 4), vcol = tid & 15;
   const TV* __restrict__ Vp = V + vrow * ldv + vcol;
-  double rv[8], rb[4];
+  double rv[MB], rb[4];
   auto gload = [&](int64_t k0) {
     const bool kin = k0 + vcol < k_end;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < MB; ++j)
       rv[j] = (kin && vrow + 16 * j < M) ? (double)Vp[16 * j * ldv + k0] : 0.0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -238,7 +240,7 @@ __global__ __launch_bounds__(256) void k_dgemm_rhs(int64_t M, int64_t Nn, int64_
   };
   auto stage = [&](int buf) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) Vs[buf][(tid >> 4) + 16 * j][vcol] = rv[j];
+    for (int j = 0; j < MB; ++j) Vs[buf][(tid >> 4) + 16 * j][vcol] = rv[j];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int e = tid + 256 * j;
@@ -258,15 +260,12 @@ __global__ __launch_bounds__(256) void k_dgemm_rhs(int64_t M, int64_t Nn, int64_
 #pragma unroll
     for (int ks = 0; ks < kDK; ks += 4) {
       const int kr = ks + (lane >> 4);
-      double av[4], bv[2];
+      double av[MB];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) av[a] = Vs[buf][wm * 64 + a * 16 + (lane & 15)][kr];
+      for (int a = 0; a < MB; ++a) av[a] = Vs[buf][a * 16 + (lane & 15)][kr];
+      const double bv = Bs[buf][w * 16 + (lane & 15)][kr];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) bv[b] = Bs[buf][wn * 32 + b * 16 + (lane & 15)][kr];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+      for (int a = 0; a < MB; ++a) acc[a] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv, acc[a], 0, 0, 0);
     }
     // the other buffer was last read before the previous barrier
     if (more) stage(buf ^ 1);
@@ -275,16 +274,36 @@ __global__ __launch_bounds__(256) void k_dgemm_rhs(int64_t M, int64_t Nn, int64_
   }
   out += (int64_t)blockIdx.z * so;
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < MB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        // f64 16x16 output: element r of lane l is row 4 r + l / 16, column l % 16
-        const int64_t m = m0 + wm * 64 + a * 16 + 4 * r + (lane >> 4);
-        const int64_t n = n0 + wn * 32 + b * 16 + (lane & 15);
-        if (m < M && n < Nn) out[m * ldo + n] = acc[a][b][r];
-      }
+    for (int r = 0; r < 4; ++r) {
+      // f64 16x16 output: element r of lane l is row 4 r + l / 16, column l % 16
+      const int64_t m = m0 + a * 16 + 4 * r + (lane >> 4);
+      const int64_t n = n0 + w * 16 + (lane & 15);
+      if (m < M && n < Nn) out[m * ldo + n] = acc[a][r];
+    }
+}
+
+// MB for M vectors in tiles of at most kDM, all alike
+template <typename TV, typename TA, bool TRANSB>
+static void launch_dgemm_rhs(int64_t M, int64_t Nn, int64_t K, const TV* V, int64_t ldv, const TA* A, int64_t lda,
+                             int64_t kc, int nz, double* out, int64_t ldo, int64_t so, hipStream_t st) {
+  const int64_t mt = (M + kDM - 1) / kDM;
+  const int mb = (int)(((M + mt - 1) / mt + 15) / 16);
+  const dim3 grid((unsigned)((Nn + kDN - 1) / kDN), (unsigned)mt, (unsigned)nz);
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, M, Nn, K, V, ldv, A, lda, kc, out, ldo, so);
+  };
+  switch (mb) {
+    case 1: go(k_dgemm_rhs<TV, TA, TRANSB, 1>); break;
+    case 2: go(k_dgemm_rhs<TV, TA, TRANSB, 2>); break;
+    case 3: go(k_dgemm_rhs<TV, TA, TRANSB, 3>); break;
+    case 4: go(k_dgemm_rhs<TV, TA, TRANSB, 4>); break;
+    case 5: go(k_dgemm_rhs<TV, TA, TRANSB, 5>); break;
+    case 6: go(k_dgemm_rhs<TV, TA, TRANSB, 6>); break;
+    case 7: go(k_dgemm_rhs<TV, TA, TRANSB, 7>); break;
+    default: go(k_dgemm_rhs<TV, TA, TRANSB, 8>); break;
+  }
 }
 
 // cs[a][n] = q w~_a / sigma_n (0 past the constraints): the scale of a count
@@ -2012,14 +2031,12 @@ static hipError_t colsum(const Ctx& X, const TV* v) {
   if (X.dense_rhs) {
     // chunk z of the orbits writes slab z of the partials (X.dcs chunks)
     const int64_t n_a = X.L.NA, kc = (n_a + X.dcs - 1) / X.dcs;
-    const dim3 grid((unsigned)((X.L.C + kDN - 1) / kDN), (unsigned)((X.L.P + kDM - 1) / kDM), (unsigned)X.dcs);
-    if (X.dtype == SW_F32)
-      hipLaunchKernelGGL((k_dgemm_rhs<TV, float, false>), grid, dim3(256), 0, X.st, (int64_t)X.L.P, X.L.C, n_a, v,
-                         n_a, (const float*)X.A, X.L.C, kc, X.p<double>(X.L.off_part), (int64_t)kSlabs * X.L.C, X.L.C);
-    else
-      hipLaunchKernelGGL((k_dgemm_rhs<TV, double, false>), grid, dim3(256), 0, X.st, (int64_t)X.L.P, X.L.C, n_a, v,
-                         n_a, (const double*)X.A, X.L.C, kc, X.p<double>(X.L.off_part), (int64_t)kSlabs * X.L.C,
-                         X.L.C);
+    const auto go = [&](auto* A) {
+      launch_dgemm_rhs<TV, std::remove_cv_t<std::remove_pointer_t<decltype(A)>>, false>(
+          X.L.P, X.L.C, n_a, v, n_a, A, X.L.C, kc, X.dcs, X.p<double>(X.L.off_part), (int64_t)kSlabs * X.L.C, X.L.C, X.st);
+    };
+    if (X.dtype == SW_F32) go((const float*)X.A);
+    else go((const double*)X.A);
     return hipGetLastError();
   }
   if (X.sparse && X.L.rg > 1) {
@@ -2126,9 +2143,8 @@ static void launch_rowdot(const Ctx& X, const RowArgs& R) {
     const int64_t n_a = X.L.NA, kc = ((X.L.C + X.drd - 1) / X.drd + kDK - 1) / kDK * kDK;
     const int nz = (int)((X.L.C + kc - 1) / kc);
     double* pd = X.p<double>(X.L.off_pd);
-    const dim3 grid((unsigned)((n_a + kDN - 1) / kDN), (unsigned)((X.L.P + kDM - 1) / kDM), (unsigned)nz);
-    hipLaunchKernelGGL((k_dgemm_rhs<double, TA, true>), grid, dim3(256), 0, X.st, (int64_t)X.L.P, n_a, X.L.C, sc, X.L.Cp,
-                       (const TA*)X.A, X.L.C, kc, pd, (int64_t)nz * n_a, n_a);
+    launch_dgemm_rhs<double, TA, true>(X.L.P, n_a, X.L.C, sc, X.L.Cp, (const TA*)X.A, X.L.C, kc, nz, pd,
+                                       (int64_t)nz * n_a, n_a, X.st);
     hipLaunchKernelGGL(k_rowdot_fin, dim3(blocks_for(n_a), (unsigned)X.L.P), dim3(256), 0, X.st, nz, (const double*)pd,
                        R);
     return;

@@ -109,6 +109,28 @@ def test_one_data_vector_is_solve_weights(gpu):
     assert np.array_equal(w_s, w_m[0])
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_dense_passes_in_every_tile_height(gpu, dtype):
+    """Dense MFMA passes over 8 to 128 data vectors (tiles of 16 to 128 of them, full and ragged): every vector's sums
+    keep their order whatever the tile, so the first vectors' weights are the same to the bit in all of them."""
+    P = lib()
+    n, c, cb = 530, 201, 70
+    blocks = [(0, cb), (cb, c)]
+    A = W.sparse_lognormal_matrix(n, blocks, density=0.3, seed=6).astype(dtype)
+    d, sig, wt = mock_problem(A, blocks, 4, 0.02, 0.02)
+    D = BS.bootstrap_data(d, sig, W.bootstrap_eps(128, c, seed=1), cb, c)
+    old = P.get_tuning("multi_dense")
+    P.set_tuning("multi_dense", 1)
+    try:
+        out = {m: multi_solve(A, D[:m], sig, wt)[0][:8] for m in (8, 16, 17, 33, 64, 65, 81, 97, 112, 113, 128)}
+    finally:
+        P.set_tuning("multi_dense", old)
+    for m in out:
+        assert np.array_equal(out[m], out[8]), m
+    w_o, _ = oracle_solve(A, D[0], sig, wt, 1e-2)
+    assert np.abs(out[8][0] - w_o).sum() / np.abs(w_o).sum() < W_L1_TOL
+
+
 def test_multi_rhs_agrees_with_separate_solves_dense_and_masked(gpu):
     """Dense matrix (uncompressed passes) and masked orbits: each realisation
     agrees with its own solve_weights call."""
