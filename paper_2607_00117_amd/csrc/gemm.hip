@@ -569,108 +569,192 @@ __global__ __launch_bounds__(kThreads) void k_zero_block(float* __restrict__ out
 }
 
 // ---------------------------------------------------------------------------
-// Diagonal block of the factorisation: unblocked right-looking Cholesky of a
-// 128 x 128 block fused with the inverse of its factor by right-looking
-// forward substitution on the identity; the factor overwrites the block and
-// its inverse goes to dinv.  The block lives in registers: thread (ty, tx) of
-// a 32 x 32 grid owns the elements (ty + 32p, tx + 32q), p, q < 4, a cyclic
-// layout that keeps every thread busy down to the last columns.  Step k
-// finishes column k of the factor and row k of the inverse, broadcasts them
-// through LDS with the entries that must not change set to zero, and applies
-// both rank-1 updates as 32 unconditional fused multiply-adds per thread,
-// which leave finished rows and columns exactly as they are.  A non-positive
-// pivot sets *bad and is replaced by a tiny positive value so the factor stays
-// finite.
+// Diagonal block of the factorisation: right-looking Cholesky of a 128 x 128
+// block and the inverse of its factor by right-looking forward substitution on
+// the identity; the factor overwrites the block and its inverse goes to dinv.
+// One workgroup with both in LDS, in panels of 32 columns: one wave factors the
+// panel's 32 x 32 block in registers (lane i its row i, the other rows' entries
+// by lane reads), a thread per row below finishes the panel's columns while a
+// thread per column finishes the panel's rows of the inverse, and all threads
+// then apply the panel's 32 rank-1 updates to what is left.  Every entry takes its
+// updates one fused multiply-add per step in the order of the steps, as the
+// unblocked form does.  Bound by the chain of 128 pivots; a barrier and a
+// full-block update per step took 105 us, 13 barriers and the updates that count
+// 53 us.  A non-positive pivot sets *bad and is replaced by a tiny positive
+// value so the factor stays finite.
 // ---------------------------------------------------------------------------
-constexpr int kPotrfThreads = 1024;
+constexpr int kPotrfThreads = 512;
+constexpr int kPan = 32, kPLd = kNB + 4;  // panel; rows padded so that 16-byte reads down a column fall in distinct banks
+static_assert(kNB == 4 * kPan && kPotrfThreads == 16 * kPan, "k_potrf_diag's layout");
+
+// the panel P's updates of the blocks below and to the right of it
+template <int P>
+__device__ __forceinline__ void potrf_trail(float (*As)[kPLd], float (*Xs)[kPLd], int tx, int ty) {
+  constexpr int B = 3 - P;  // row blocks left
+  float a[B][B], x[B][P + 1];
+#pragma unroll
+  for (int u = 0; u < B; ++u) {
+    const int i = ty + kPan * (P + 1 + u);
+#pragma unroll
+    for (int v = 0; v <= u; ++v) a[u][v] = As[i][tx + kPan * (P + 1 + v)];
+#pragma unroll
+    for (int q = 0; q <= P; ++q) x[u][q] = Xs[i][tx + kPan * q];
+  }
+#pragma unroll 2
+  for (int k = kPan * P; k < kPan * (P + 1); k += 4) {
+    f32x4v ci[B], cj[B];
+    float rj[P + 1][4];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      ci[u] = *reinterpret_cast<const f32x4v*>(&As[ty + kPan * (P + 1 + u)][k]);
+      cj[u] = *reinterpret_cast<const f32x4v*>(&As[tx + kPan * (P + 1 + u)][k]);
+    }
+#pragma unroll
+    for (int q = 0; q <= P; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rj[q][e] = Xs[k + e][tx + kPan * q];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+#pragma unroll
+        for (int v = 0; v <= u; ++v) a[u][v] -= ci[u][e] * cj[v][e];
+#pragma unroll
+        for (int q = 0; q <= P; ++q) x[u][q] -= ci[u][e] * rj[q][e];
+      }
+  }
+#pragma unroll
+  for (int u = 0; u < B; ++u) {
+    const int i = ty + kPan * (P + 1 + u);
+#pragma unroll
+    for (int v = 0; v <= u; ++v) As[i][tx + kPan * (P + 1 + v)] = a[u][v];
+#pragma unroll
+    for (int q = 0; q <= P; ++q) Xs[i][tx + kPan * q] = x[u][q];
+  }
+}
+
+__device__ __forceinline__ float lane_float(float v, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
 
 __global__ __launch_bounds__(kPotrfThreads) void k_potrf_diag(float* __restrict__ Kd, int64_t ld, int64_t sK,
                                                               float* __restrict__ dinv, int64_t sD,
                                                               int* __restrict__ bad) {
   Kd += blockIdx.x * sK;
   dinv += blockIdx.x * sD;
-  __shared__ float col[kNB];  // column k of the factor below the diagonal, 0 elsewhere
-  __shared__ float row[kNB];  // row k of the inverse
-  __shared__ float dg[kNB];   // pending pivot of each step
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  float a[4][4], x[4][4];
+  __shared__ __attribute__((aligned(16))) float As[kNB][kPLd], Xs[kNB][kPLd];
+  __shared__ __attribute__((aligned(16))) float Lt[kPan][kPan];  // Lt[k][i]: entry (i, k) of the panel's square block
+  __shared__ float ips[kPan];                                    // reciprocals of its diagonal
+  const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
 #pragma unroll
-  for (int p = 0; p < 4; ++p)
+  for (int p = 0; p < kNB / 16; ++p)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int i = ty + 32 * p, j = tx + 32 * q;
-      a[p][q] = (j <= i) ? Kd[(int64_t)i * ld + j] : 0.0f;
-      x[p][q] = (i == j) ? 1.0f : 0.0f;
+      const int i = ty + 16 * p, j = tx + kPan * q;
+      const float v = Kd[(int64_t)i * ld + j];
+      As[i][j] = (j <= i) ? v : 0.0f;
+      Xs[i][j] = (i == j) ? 1.0f : 0.0f;
     }
-  if (threadIdx.x == 0) dg[0] = a[0][0];
   __syncthreads();
-  for (int k = 0; k < kNB; ++k) {
-    const int pk = k >> 5, rk = k & 31;
-    float piv = dg[k];
-    if (!(piv > 0.0f)) {
-      if (threadIdx.x == 0) atomicExch(bad, 1);
-      piv = 1e-30f;
-    }
-    piv = sqrtf(piv);
-    const float ip = 1.0f / piv;
-    if (tx == rk) {  // owners of column k
+  for (int r0 = 0; r0 < kNB; r0 += kPan) {
+    if (tid < 64) {
+      int i = tid & 31;
+      asm volatile("" : "+v"(i));  // its 64 comparisons below are made again in each panel, not kept
+      float a[kPan];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (q != pk) continue;
+      for (int j = 0; j < kPan; j += 4) *reinterpret_cast<f32x4v*>(a + j) = *reinterpret_cast<const f32x4v*>(&As[r0 + i][r0 + j]);
+      bool ok = true;
+      float piv, ip, ipv = 0.0f;
+      const auto pivot = [&](int k) {
+        piv = lane_float(a[k], k);
+        ok &= piv > 0.0f;
+        piv = sqrtf(piv > 0.0f ? piv : 1e-30f);
+        ip = 1.0f / piv;
+        ipv = i == k ? ip : ipv;
+      };
+      pivot(0);
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const int i = ty + 32 * p;
-          const float v = (i > k) ? a[p][q] * ip : 0.0f;
-          if (i > k) a[p][q] = v;
-          if (i == k) a[p][q] = piv;
-          col[i] = v;
+      for (int k = 0; k < kPan; ++k) {
+        const float l = i > k ? a[k] * ip : 0.0f;
+        a[k] = i > k ? l : (i == k ? piv : a[k]);
+        Lt[k][i] = a[k];  // the other rows' entries come back as broadcasts (both halves of the wave write the same)
+        if (k + 1 < kPan) {
+          a[k + 1] -= l * lane_float(l, k + 1);
+          pivot(k + 1);  // its chain runs beside the step's other updates
+        }
+#pragma unroll
+        for (int j0 = (k + 2) & ~3; j0 < kPan; j0 += 4) {
+          const f32x4v lj = *reinterpret_cast<const f32x4v*>(&Lt[k][j0]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (j0 + e >= k + 2) a[j0 + e] -= l * lj[e];
         }
       }
-    }
-    if (ty == rk) {  // owners of row k of the inverse: final once scaled by 1/L_kk
+      if (!ok && tid == 0) atomicExch(bad, 1);
+      if (tid < kPan) {
+        ips[i] = ipv;
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        if (p != pk) continue;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          x[p][q] *= ip;
-          row[tx + 32 * q] = x[p][q];
-        }
+        for (int j = 0; j < kPan; j += 4) *reinterpret_cast<f32x4v*>(&As[r0 + i][r0 + j]) = *reinterpret_cast<f32x4v*>(a + j);
       }
     }
     __syncthreads();
-    float ci[4], cj[4], rj[4];
+    if (tid < kNB) {
+      const int i = r0 + kPan + tid;  // a row below the panel
+      if (i < kNB) {
+        float a[kPan];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) ci[p] = col[ty + 32 * p];
+        for (int j = 0; j < kPan; j += 4) *reinterpret_cast<f32x4v*>(a + j) = *reinterpret_cast<const f32x4v*>(&As[i][r0 + j]);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      cj[q] = col[tx + 32 * q];
-      rj[q] = row[tx + 32 * q];
+        for (int k = 0; k < kPan; ++k) {
+          a[k] *= ips[k];
+#pragma unroll
+          for (int j0 = (k + 1) & ~3; j0 < kPan; j0 += 4) {
+            const f32x4v lj = *reinterpret_cast<const f32x4v*>(&Lt[k][j0]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (j0 + e > k) a[j0 + e] -= a[k] * lj[e];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < kPan; j += 4) *reinterpret_cast<f32x4v*>(&As[i][r0 + j]) = *reinterpret_cast<f32x4v*>(a + j);
+      }
+    } else if (tid < 2 * kNB) {
+      const int j = tid - kNB;  // a column of the inverse; those right of the panel are still zero in its rows
+      if (j < r0 + kPan) {
+        float x[kPan];
+#pragma unroll
+        for (int i = 0; i < kPan; ++i) x[i] = Xs[r0 + i][j];
+#pragma unroll
+        for (int k = 0; k < kPan; ++k) {
+          x[k] *= ips[k];
+#pragma unroll
+          for (int i0 = (k + 1) & ~3; i0 < kPan; i0 += 4) {
+            const f32x4v li = *reinterpret_cast<const f32x4v*>(&Lt[k][i0]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (i0 + e > k) x[i0 + e] -= li[e] * x[k];
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < kPan; ++i) Xs[r0 + i][j] = x[i];
+      }
     }
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        a[p][q] -= ci[p] * cj[q];
-        x[p][q] -= ci[p] * rj[q];
-      }
-    if (k + 1 < kNB) {
-      const int k1 = k + 1, r1 = k1 & 31, p1 = k1 >> 5;
-      if (tx == r1 && ty == r1) {
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-          if (p == p1) dg[k1] = a[p][p];
-      }
+    __syncthreads();
+    for (int t = ty; t < kPan; t += 16) {
+      if (r0 == 0) potrf_trail<0>(As, Xs, tx, t);
+      else if (r0 == kPan) potrf_trail<1>(As, Xs, tx, t);
+      else if (r0 == 2 * kPan) potrf_trail<2>(As, Xs, tx, t);
     }
     __syncthreads();
   }
 #pragma unroll
-  for (int p = 0; p < 4; ++p)
+  for (int p = 0; p < kNB / 16; ++p)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int i = ty + 32 * p, j = tx + 32 * q;
-      Kd[(int64_t)i * ld + j] = (j <= i) ? a[p][q] : 0.0f;
-      dinv[i * kNB + j] = (j <= i) ? x[p][q] : 0.0f;
+      const int i = ty + 16 * p, j = tx + kPan * q;
+      const float v = As[i][j], x = Xs[i][j];
+      Kd[(int64_t)i * ld + j] = (j <= i) ? v : 0.0f;
+      dinv[i * kNB + j] = (j <= i) ? x : 0.0f;
     }
 }
 

@@ -310,6 +310,30 @@ def test_history_passes_at_their_block_edges(gpu, together):
             assert kkt <= 1.5 * max(reps[k - k0].kkt, 1e-7)
 
 
+@pytest.mark.parametrize("c", [1, 31, 33, 64, 97, 127, 128, 129, 300])
+def test_factor_block_edges(gpu, c):
+    """Constraint counts around the 128-column blocks of the factorisation and their 32-column panels: the factor's
+    inverse preconditions every iteration, so a wrong entry shows as a solve that does not converge; the weights meet
+    the KKT conditions of the oracle."""
+    import torch
+    P = lib()
+    rng = np.random.default_rng(c)
+    n = 150
+    A = np.where(rng.random((n, c)) < 0.5, rng.random((n, c)), 0.0) + 0.01
+    d = (A.T @ rng.exponential(1.0, n)) * (1 + 0.02 * rng.normal(size=c))
+    sig = 0.02 * d
+    opts = P._lib.SolveOpts()
+    opts.gram, opts.nu, opts.refine_iter = 2, 1e-2, 400
+    w = torch.empty(n, dtype=torch.float64, device=gpu)
+    ws = torch.full((P.solve_workspace_bytes(n, c, opts),), 255, dtype=torch.uint8, device=gpu)
+    status, rep = P.solve_weights(torch.from_numpy(A).to(gpu), torch.from_numpy(d).to(gpu), torch.from_numpy(sig).to(gpu),
+                                  1.0, -1.0, opts, w, ws)
+    assert status == 0 and rep.converged == 1
+    U, y = N.scale_problem(A, d, sig, 1.0)
+    kkt = N.kkt_residual(U, y, rep.mu, w.cpu().numpy()) / np.abs(U.T @ y).max()
+    assert kkt <= 1.5 * max(rep.kkt, 1e-7)
+
+
 def test_solve_dense_matrix_path(gpu):
     """A fully dense matrix takes the uncompressed passes over A."""
     rng = np.random.default_rng(12)
