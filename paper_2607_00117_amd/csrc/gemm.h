@@ -58,9 +58,18 @@ hipError_t spd_inverse_factor(float* S, int64_t n, int64_t ld, int64_t sK, float
 
 // s_b = (L_b L_b^T)^-1 r_b = W^T (W r_b) from S_b (fp32, vectors of length n at
 // stride sv; tmp: scratch of the same shape).  Problems with act[b * act_stride]
-// == 0 are skipped (act may be null).
+// == 0 are skipped (act may be null).  cs: where inv_apply_scales() holds, also
+// sc_b[i] = par_b[0] s_b[i] / sigma_b[i] for i < C, from the kernel that writes s.
+struct ColScale {
+  const double* par;  // at par_stride per problem
+  int par_stride;
+  const double* sigma;  // at sS per problem
+  int64_t sS, C;
+  double* sc;  // at sv per problem
+};
+bool inv_apply_scales(int64_t n);
 hipError_t inv_apply(const float* S, int64_t n, int64_t ld, int64_t sK, int nb, const float* r, float* tmp, float* s,
-                     int64_t sv, const double* act, int act_stride, hipStream_t st);
+                     int64_t sv, const double* act, int act_stride, hipStream_t st, const ColScale& cs = ColScale{});
 
 // The same for P right-hand sides of one S (r, tmp, s: [P] vectors at stride
 // sv): from kTrmmMinRhs of them on, two MFMA passes that read each half of S

@@ -884,7 +884,8 @@ template <bool LOWER, bool SMALL>
 __global__ __launch_bounds__(SMALL ? 64 : kThreads) void k_trmv16(const float* __restrict__ S, int64_t n, int64_t ld,
                                                                   int64_t sK, const float* __restrict__ x,
                                                                   float* __restrict__ y, int64_t sv,
-                                                                  const double* __restrict__ act, int act_stride) {
+                                                                  const double* __restrict__ act, int act_stride,
+                                                                  ColScale cs) {
   const int64_t b = blockIdx.y;
   if (act && act[b * act_stride] == 0.0) return;
   S += b * sK;
@@ -958,14 +959,19 @@ __global__ __launch_bounds__(SMALL ? 64 : kThreads) void k_trmv16(const float* _
       add(jb, c);
     }
   }
+  float out = 0.0f;  // lane l < 16: the sum of its row
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
       float v = acc[h][r];
       for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-      if (lane == 0) y[R[h] + r] = v;
+      out = lane == 8 * h + r ? v : out;
     }
+  if (lane >= 16) return;
+  const int64_t i = (lane < 8 ? R[0] : R[1]) + (lane & 7);
+  y[i] = out;
+  if (!LOWER && cs.sc && i < cs.C) cs.sc[b * sv + i] = cs.par[b * cs.par_stride] * (double)out / cs.sigma[b * cs.sS + i];
 }
 
 // ---------------------------------------------------------------------------
@@ -1330,14 +1336,16 @@ hipError_t inv_apply_rhs(const float* S, int64_t n, int64_t ld, int P, const flo
   return hipGetLastError();
 }
 
+bool inv_apply_scales(int64_t n) { return n % 16 == 0 && g_trmv_rows == 16; }
+
 hipError_t inv_apply(const float* S, int64_t n, int64_t ld, int64_t sK, int nb_prob, const float* r, float* tmp,
-                     float* s, int64_t sv, const double* act, int act_stride, hipStream_t st) {
-  if (n % 16 == 0 && g_trmv_rows == 16) {
+                     float* s, int64_t sv, const double* act, int act_stride, hipStream_t st, const ColScale& cs) {
+  if (inv_apply_scales(n)) {
     const bool small = n / 16 * nb_prob <= kTrmvSmall;
     const unsigned g = (unsigned)(small ? n / 16 : (n / 16 + kThreads / 64 - 1) / (kThreads / 64));
     const auto go = [&](auto kernel, const float* in, float* out) {
       hipLaunchKernelGGL(kernel, dim3(g, (unsigned)nb_prob), dim3(small ? 64 : kThreads), 0, st, S, n, ld, sK, in, out,
-                         sv, act, act_stride);
+                         sv, act, act_stride, cs);
     };
     if (small) {
       go(k_trmv16<true, true>, r, tmp);
