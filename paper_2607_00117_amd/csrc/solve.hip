@@ -2053,7 +2053,10 @@ static void launch_csc_colsum(const Ctx& X, dim3 grid, int cpw, int64_t len, con
                        X.p<int64_t>(X.L.off_cptr), X.p<uint16_t>(X.L.off_crow), X.p<TA>(X.L.off_cval), v, X.par,
                        X.L.shared ? 1 : 0, o);
   };
-  if (small_wg(len, grid)) go(k_csc_colsum<TA, TV, 256, kSmallVec, true>, 256);
+  // pipelined sums for 16-bit counts only: wider values loaded ahead do not fit the
+  // registers (64 problems of 2,000 orbits, 60 iterations: FP32 values 46.0 ms
+  // pipelined, 42.9 not; FP64 79.7 and 50.6; both 57 and 66 in 16-wave workgroups)
+  if (small_wg(len, grid)) go(k_csc_colsum<TA, TV, 256, kSmallVec, sizeof(TA) == 2>, 256);
   else go(k_csc_colsum<TA, TV, kSpThreads, kBlk, false>, kSpThreads);
 }
 
