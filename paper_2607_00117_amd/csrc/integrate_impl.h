@@ -12,14 +12,16 @@
 // Event word (uint64, one per orbit per step per block): four 16-bit cell
 // indices, copy c in bits [16c, 16c+16), 0xFFFF = outside the block.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 
 #include "potential.h"
 
 namespace sw {
 
-constexpr int kStage = 16;
+constexpr int kStage = 16;  // staged steps of a tile (half where the LDS of several tiles shares a workgroup)
 constexpr int kWave = 64;
+constexpr int kTileWaves = 4;  // tiles per workgroup of k_integrate, at most
 
 // lamw: the single-precision path's warm-start state of the bar's lam (unused in double)
 template <typename T>
@@ -208,7 +210,18 @@ __device__ __forceinline__ void write_stage(const uint64_t (*stm)[OPW + 1], cons
   }
 }
 
-// One wave does all of a tile's work.  At most 168 registers, so that three waves share a SIMD (the default
+// A wave's own LDS exchange: writes before, reads after, no other wave involved.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One wave does all of a tile's work; a workgroup carries up to kTileWaves tiles,
+// which share nothing: the waves of a workgroup are spread over the SIMDs of its
+// CU, while workgroups of one wave may meet on one SIMD with others idle (the
+// barred model in FP64, 300 steps, 1,024 tiles: 8.3 ms in workgroups of one
+// tile, 5.1 of four).  At most 168 registers, so that three waves share a SIMD (the default
 // allocation lands one register above that, at two waves); no spills.
 //
 // LPO lanes per orbit (1, or 2 in single precision): a wave carries 64 / LPO
@@ -216,20 +229,23 @@ __device__ __forceinline__ void write_stage(const uint64_t (*stm)[OPW + 1], cons
 // the force and the pair adds the shares, so both advance identically; the
 // first lane of the pair writes the orbit's events and results.
 template <typename T, int MODE, bool BIN, int LPO = 1, bool NB = false, bool CYL = false>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(kTileWaves* kWave) __attribute__((amdgpu_waves_per_eu(3)))
 void k_integrate(const PotK p0, const sw_potential* __restrict__ pots, const int64_t* __restrict__ offsets,
                  int32_t n_pot, ObsK O, const T* __restrict__ ics, const T* __restrict__ dts, int64_t n_orb,
                  int64_t orb0, int64_t n_chunk, int32_t n_steps, uint64_t* __restrict__ ev_m,
                  uint64_t* __restrict__ ev_k, double* __restrict__ drift, uint8_t* __restrict__ flags,
                  T* __restrict__ final_state) {
   constexpr int OPW = kWave / LPO;  // orbits per wave
-  __shared__ uint64_t stm[kStage][OPW + 1];
-  __shared__ uint64_t stk[kStage][OPW + 1];
-  const int lane = threadIdx.x;
+  constexpr int ST = kStage / 2;
+  __shared__ uint64_t staged[kTileWaves][2][ST][OPW + 1];
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int nw = blockDim.x / kWave;
+  auto& stm = staged[wave][0];
+  auto& stk = staged[wave][1];
   const int part = lane % LPO, lo = lane / LPO;  // share and orbit of this lane
   const int64_t n_tiles = tile_count<OPW>(MODE, n_pot, n_chunk);
-  // persistent launch: each wave walks the orbit tiles t = blockIdx.x, + gridDim.x, ...
-  for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+  // persistent launch: each wave walks the orbit tiles at the stride of the grid's waves
+  for (int64_t tile = (int64_t)blockIdx.x * nw + wave; tile < n_tiles; tile += (int64_t)gridDim.x * nw) {
     const Tile tl = tile_at<MODE, OPW>(tile, offsets, n_pot, orb0, n_chunk);
     if (tl.cnt == 0) continue;
     const bool valid = lo < tl.cnt;
@@ -257,10 +273,10 @@ void k_integrate(const PotK p0, const sw_potential* __restrict__ pots, const int
           stk[slot][lo] = pack4(kc);
         }
         ++slot;
-        if (slot == kStage || k == n_steps) {
-          __syncthreads();
-          write_stage<kStage, OPW>(stm, stk, slot, tl, n_steps, k - slot, lane, ev_m, ev_k);
-          __syncthreads();
+        if (slot == ST || k == n_steps) {
+          wave_fence();
+          write_stage<ST, OPW>(stm, stk, slot, tl, n_steps, k - slot, lane, ev_m, ev_k);
+          wave_fence();
           slot = 0;
         }
       }
@@ -356,14 +372,9 @@ void k_integrate_split(const PotK p0, const sw_potential* __restrict__ pots, con
         }
       }
       if (slot == ST || (bins && r == n_rounds - 1)) {
-        // this wave alone stages and reads back
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_fence();  // this wave alone stages and reads back
         write_stage<ST, kWave>(stm, stk, slot, tl, n_steps, r * kHand + n - slot, lane, ev_m, ev_k);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_fence();
         slot = 0;
       }
     }
@@ -429,11 +440,13 @@ void launch_integrate_v(const IntegrateLaunch& L, hipStream_t st) {
     const int64_t cap = (int64_t)g_waves_per_cu * g_num_cus;
     if (tiles > cap) tiles = cap;
   }
-  const dim3 grid((unsigned)tiles);
+  // one-wave tiles per workgroup: as few as leave one workgroup per CU
+  const int nw = (int)std::min<int64_t>(kTileWaves, (tiles + g_num_cus - 1) / g_num_cus);
+  const dim3 grid((unsigned)tiles), grid1((unsigned)((tiles + nw - 1) / nw));
   const T* ics = (const T*)L.ics;
   const T* dt = (const T*)L.dt;
   const auto one = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(kWave), 0, st, L.p0, L.pots_dev, L.offsets_dev, L.n_pot, L.obs, ics, dt,
+    hipLaunchKernelGGL(kernel, grid1, dim3(nw * kWave), 0, st, L.p0, L.pots_dev, L.offsets_dev, L.n_pot, L.obs, ics, dt,
                        L.n_orb, L.orb0, L.n_chunk, L.n_steps, L.ev_m, L.ev_k, L.drift, L.flags, (T*)L.final_state);
   };
   const auto split = [&](auto kernel) {
