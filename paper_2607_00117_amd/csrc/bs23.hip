@@ -28,6 +28,8 @@
 //     30,000 x 5,000 steps of the barred model in FP32: 107.5 ms in one wave with
 //     common steps, 44.9 now (54.9 with one drift wave, 46.7 without a raised
 //     priority for the integrating waves).
+//     FP64 and needle-bar launches of more tiles than the CUs hold of these
+//     workgroups take one wave per tile (k_bs23_one; shares_tile has the figures).
 //  2. k_hist_w: one workgroup per orbit (and window of columns when a row does
 //     not fit LDS): each event's weight dt_k / t_total is rounded to a 64-bit
 //     fixed-point integer in units of 2^-52 and added into an LDS histogram of
@@ -40,13 +42,17 @@
 //     took 6.2 ms in five passes, 4.0 now.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "common.h"
 #include "potential.h"
 
 namespace sw {
+extern int g_num_cus;
+
 namespace {
 
 constexpr int kBsWindow = 20000;  // histogram columns per pass (160,000 bytes of LDS)
@@ -102,6 +108,39 @@ __device__ __forceinline__ double bs_jacobi(const PotK& P, const float* y, float
 __device__ __forceinline__ double bs_pow(double e) { return pow(e, -1.0 / 3.0); }
 __device__ __forceinline__ float bs_pow(float e) { return powf(e, -1.0f / 3.0f); }
 
+// One attempt at a step of length h: true when it is accepted (y and k1 then
+// are the new state's); hh is the length it tried, h that of the next one.
+template <bool NB, typename T>
+__device__ __forceinline__ bool bs_attempt(const PotK& P, T* y, T* k1, T& h, float& lamw, T rt, T at, T& hh) {
+#pragma clang fp contract(off)
+  hh = h;
+  T t[6], k2[6], k3[6], y3[6], k4[6];
+  for (int i = 0; i < 6; ++i) t[i] = y[i] + (T)0.5 * hh * k1[i];
+  bs_rhs<NB>(P, t, k2, lamw);
+  for (int i = 0; i < 6; ++i) t[i] = y[i] + (T)0.75 * hh * k2[i];
+  bs_rhs<NB>(P, t, k3, lamw);
+  for (int i = 0; i < 6; ++i)
+    y3[i] = y[i] + hh * ((T)(2.0 / 9.0) * k1[i] + (T)(1.0 / 3.0) * k2[i] + (T)(4.0 / 9.0) * k3[i]);
+  bs_rhs<NB>(P, y3, k4, lamw);
+  T err = (T)0;
+  for (int i = 0; i < 6; ++i) {
+    const T y2 = y[i] + hh * ((T)(7.0 / 24.0) * k1[i] + (T)0.25 * k2[i] + (T)(1.0 / 3.0) * k3[i] + (T)0.125 * k4[i]);
+    const T sc = at + rt * fmax(fabs(y[i]), fabs(y3[i]));
+    err = fmax(err, fabs(y3[i] - y2) / sc);
+  }
+  T fac = err > (T)0 ? (T)0.9 * bs_pow(err) : (T)5;
+  fac = fmin((T)5, fmax((T)0.2, fac));
+  h = hh * fac;
+  const bool ok = err <= (T)1;
+  if (ok) {
+    for (int i = 0; i < 6; ++i) {
+      y[i] = y3[i];
+      k1[i] = k4[i];
+    }
+  }
+  return ok;
+}
+
 // accepted steps handed from the integrating wave to the others
 template <typename T>
 struct BsRound {
@@ -114,7 +153,7 @@ struct BsRound {
 // T: the arithmetic of the state, the stages and the step control (the total
 // time is summed in double, the Jacobi drift evaluated in double)
 template <typename T, bool NB, bool CYL>
-__global__ __launch_bounds__(kBsThreads) void k_bs23(PotK P, ObsK O, const double* __restrict__ ics,
+__global__ __launch_bounds__(kBsThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && CYL ? 2 : 1))) void k_bs23(PotK P, ObsK O, const double* __restrict__ ics,
                                                       const double* __restrict__ h0, int64_t n, int32_t S,
                                                       double rtol, double atol, uint64_t* __restrict__ ev_m,
                                                       uint64_t* __restrict__ ev_k, double* __restrict__ wts,
@@ -154,32 +193,8 @@ __global__ __launch_bounds__(kBsThreads) void k_bs23(PotK P, ObsK O, const doubl
       if (last < 0) {
         for (int a = 0; a < kRound; ++a) {
           if (s >= S) continue;
-          const T hh = h;
-          T t[6], k2[6], k3[6], y3[6], k4[6];
-          for (int i = 0; i < 6; ++i) t[i] = y[i] + (T)0.5 * hh * k1[i];
-          bs_rhs<NB>(P, t, k2, lamw);
-          for (int i = 0; i < 6; ++i) t[i] = y[i] + (T)0.75 * hh * k2[i];
-          bs_rhs<NB>(P, t, k3, lamw);
-          for (int i = 0; i < 6; ++i)
-            y3[i] = y[i] + hh * ((T)(2.0 / 9.0) * k1[i] + (T)(1.0 / 3.0) * k2[i] + (T)(4.0 / 9.0) * k3[i]);
-          bs_rhs<NB>(P, y3, k4, lamw);
-          T err = (T)0;
-          for (int i = 0; i < 6; ++i) {
-            const T y2 = y[i] + hh * ((T)(7.0 / 24.0) * k1[i] + (T)0.25 * k2[i] + (T)(1.0 / 3.0) * k3[i] +
-                                      (T)0.125 * k4[i]);
-            const T sc = at + rt * fmax(fabs(y[i]), fabs(y3[i]));
-            err = fmax(err, fabs(y3[i] - y2) / sc);
-          }
-          T fac = err > (T)0 ? (T)0.9 * bs_pow(err) : (T)5;
-          fac = fmin((T)5, fmax((T)0.2, fac));
-          h = hh * fac;
-          const bool ok = err <= (T)1;
-          if (ok) {
-            for (int i = 0; i < 6; ++i) {
-              y[i] = y3[i];
-              k1[i] = k4[i];
-            }
-          }
+          T hh;
+          const bool ok = bs_attempt<NB>(P, y, k1, h, lamw, rt, at, hh);
           ++tries;
           if (ok || tries == 100) {  // a step: accepted, or of length 0 after 100 rejections
             for (int i = 0; i < 6; ++i) R.y[got][i][lane] = y[i];
@@ -251,6 +266,57 @@ __global__ __launch_bounds__(kBsThreads) void k_bs23(PotK P, ObsK O, const doubl
   }
 }
 
+// The same in one wave per 64 orbits, without LDS, for the launches whose
+// four-wave workgroups would queue (shares_tile): the orbits of a wave take their
+// steps together, an attempt being repeated until every lane has accepted.  Bound
+// by the issue of the attempts, two waves per SIMD (about 250 registers in FP64).
+template <typename T, bool NB, bool CYL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 1))) void k_bs23_one(PotK P, ObsK O, const double* __restrict__ ics,
+                                                 const double* __restrict__ h0, int64_t n, int32_t S, double rtol,
+                                                 double atol, uint64_t* __restrict__ ev_m, uint64_t* __restrict__ ev_k,
+                                                 double* __restrict__ wts, double* __restrict__ ttot,
+                                                 double* __restrict__ drift, uint8_t* __restrict__ flags) {
+#pragma clang fp contract(off)
+  const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (o >= n) return;
+  T y[6], k1[6];
+  for (int i = 0; i < 6; ++i) y[i] = (T)ics[(int64_t)i * n + o];
+  const T rt = (T)rtol, at = (T)atol;
+  T h = (T)h0[o];
+  double tt = 0.0, dmax = 0.0;
+  float lamw = -1.0f;
+  bool bad = false;
+  bs_rhs<NB>(P, y, k1, lamw);
+  const double E0 = bs_jacobi<NB>(P, y, lamw);
+  for (int s = 0; s < S; ++s) {
+    T dt = (T)0;
+    for (int tries = 0; tries < 100; ++tries) {
+      T hh;
+      if (bs_attempt<NB>(P, y, k1, h, lamw, rt, at, hh)) {
+        dt = hh;
+        break;
+      }
+    }
+    if (dt == (T)0) bad = true;
+    for (int i = 0; i < 6; ++i)
+      if (!isfinite(y[i])) bad = true;
+    tt += (double)dt;
+    uint32_t mc[4], kc[4];
+    cells4<T, CYL>(P, O, y, mc, kc);
+    const int64_t e = o * S + s;
+    ev_m[e] = pack4(mc);
+    ev_k[e] = pack4(kc);
+    wts[e] = (double)dt;
+    if (O.drift_every > 0 && (s + 1) % O.drift_every == 0) {
+      const double d = fabs(bs_jacobi<NB>(P, y, lamw) / E0 - 1.0);
+      if (!(d <= dmax)) dmax = d;
+    }
+  }
+  ttot[o] = tt;
+  drift[o] = dmax;
+  flags[o] = (uint8_t)((!(dmax <= 0.1) ? SW_FLAG_DRIFT : 0) | (bad ? SW_FLAG_NONFINITE : 0));
+}
+
 // Columns [win0, win0 + wn) of a row; the blocks' first columns are 0, n_mass and
 // n_mass + n_kin (nv > 0: surface block, kinematic codes ap nv + v_bin and
 // n_kin + ap count in its column ap).  The window 0 also writes the overflow.
@@ -305,6 +371,23 @@ __global__ __launch_bounds__(NT) void k_hist_w(const uint64_t* __restrict__ ev_m
     row[c] = (uint32_t)(win0 + c) >= nm + nk ? v / div : v;
   }
   if (tid < 2 && win0 == 0) overflow[o * 2 + tid] = (double)ovq[tid] * scale;
+}
+
+// Whether four waves share a tile, where two such workgroups fit a CU (FP64, and
+// needle bars).  Up to two tiles per CU they are all resident, and do.  Above, the
+// next round waits, while one wave per tile still leaves a wave its SIMD up to
+// four tiles per CU and two waves share one up to eight; the tiles of a workgroup
+// are spread over the SIMDs.  40 steps of the barred model in FP64, four waves and
+// one: 32,700 orbits 2.7 and 5.0 ms, 65,500 5.2 and 5.1, 98,000 7.6 and 8.4,
+// 131,000 10.2 and 8.5, 200,000 16.9 and 15.6.  In single precision with needle
+// bars the three forces cost less next to the rest: 65,500 orbits 5.9 and 6.8, and
+// of 4 steps 1.3 and 1.2.  A few steps per orbit leave the hand-over's first and
+// last rounds: 98,000 FP64 orbits x 4 steps 1.5 and 1.3.
+bool shares_tile(int64_t tiles, int32_t n_steps, bool f64) {
+  const int64_t cus = g_num_cus;
+  if (tiles <= 2 * cus) return true;
+  if (tiles <= 4 * cus) return !f64 && n_steps >= 16;
+  return tiles <= 6 * cus && n_steps >= 32;
 }
 
 size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -364,28 +447,33 @@ extern "C" int integrate_bs23_and_bin(const sw_potential* pot, const double* ics
   double* wts = (double*)(ws + 2 * per);
   double* ttot = (double*)(ws + 3 * per);
   hipStream_t st = (hipStream_t)stream;
-  const dim3 grid((unsigned)((n_orb + 63) / 64)), block(kBsThreads);
-#define SW_BS23_LAUNCH(T, NB, CYL)                                                                                \
-  hipLaunchKernelGGL((k_bs23<T, NB, CYL>), grid, block, 0, st, P, O, ics, h0, n_orb, n_steps, rtol, atol, ev_m, ev_k, \
-                     wts, ttot, drift, flags)
-  if (precision == SW_F32) {
-    if (O.cyl) {
-      if (nb) SW_BS23_LAUNCH(float, true, true);
-      else SW_BS23_LAUNCH(float, false, true);
-    } else {
-      if (nb) SW_BS23_LAUNCH(float, true, false);
-      else SW_BS23_LAUNCH(float, false, false);
+  const auto launch = [&](auto t, auto needle, auto cyl) {
+    typedef decltype(t) T;
+    constexpr bool NB = decltype(needle)::value, CYL = decltype(cyl)::value;
+    const int64_t tiles = (n_orb + 63) / 64;
+    const auto go = [&](auto kernel, int64_t groups, int nt) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(nt), 0, st, P, O, ics, h0, n_orb, n_steps, rtol, atol,
+                         ev_m, ev_k, wts, ttot, drift, flags);
+    };
+    if constexpr (sizeof(T) == 8 || NB) {
+      if (!shares_tile(tiles, n_steps, sizeof(T) == 8)) {
+        const int64_t nw = std::min<int64_t>(4, (tiles + g_num_cus - 1) / g_num_cus);
+        go(k_bs23_one<T, NB, CYL>, (tiles + nw - 1) / nw, (int)nw * 64);
+        return;
+      }
     }
-  } else {
-    if (O.cyl) {
-      if (nb) SW_BS23_LAUNCH(double, true, true);
-      else SW_BS23_LAUNCH(double, false, true);
-    } else {
-      if (nb) SW_BS23_LAUNCH(double, true, false);
-      else SW_BS23_LAUNCH(double, false, false);
-    }
-  }
-#undef SW_BS23_LAUNCH
+    go(k_bs23<T, NB, CYL>, tiles, kBsThreads);
+  };
+  const auto with_bars = [&](auto t, auto cyl) {
+    if (nb) launch(t, std::true_type{}, cyl);
+    else launch(t, std::false_type{}, cyl);
+  };
+  const auto with_grid = [&](auto t) {
+    if (O.cyl) with_bars(t, std::true_type{});
+    else with_bars(t, std::false_type{});
+  };
+  if (precision == SW_F32) with_grid(float{});
+  else with_grid(double{});
   SW_HIP(hipGetLastError());
   const int64_t n_con = (int64_t)O.n_mass + O.n_kin + (O.surface ? O.n_ap : 0);
   return hist_w(ev_m, ev_k, wts, ttot, n_orb, n_steps, O, n_con, A, overflow, obs->upsilon, st);

@@ -193,3 +193,27 @@ def test_single_precision_small_model(gpu):
     assert np.median(l1) <= 5e-2 and tot <= 1e-2
     assert np.allclose(A[:, :1000].sum(1) + ov[:, 0], 1.0, rtol=0, atol=1e-11)
     assert np.allclose(A[:, 1000:1750].sum(1) + ov[:, 1], 1.0, rtol=0, atol=1e-11)
+
+
+@pytest.mark.parametrize("precision,comps", [(2, None), (1, "needle"), (2, "needle")])
+@pytest.mark.parametrize("grid", ["cartesian", "cylindrical"])
+def test_one_wave_per_tile_gives_the_bits_of_four(gpu, precision, comps, grid):
+    """99,001 orbits fill more than the CUs' four-wave workgroups and take one wave per 64 orbits in workgroups of four
+    tiles (the last one ragged); the same orbits 20,000 at a time take four waves: equal to the bit, one orbit of which
+    is NaN."""
+    from tests.test_gpu_batched_integrate import CYL
+    from tests.test_gpu_needle import COMPS
+    cfg = W.SMALL if comps is None else dict(W.SMALL, components=COMPS, omega=40.0)
+    obs = dict(cfg["obs"] if grid == "cartesian" else CYL, nx=5, nz=4, npx=5, npy=4, nv=5, drift_every=2)
+    rng = np.random.default_rng(6)
+    n = 99001
+    R, ph, v = rng.uniform(0.5, 8.0, n), rng.uniform(0, 2 * np.pi, n), 200.0 + rng.normal(0, 20, n)
+    ics = np.stack([R * np.cos(ph), R * np.sin(ph), rng.normal(0, 0.3, n), -v * np.sin(ph), v * np.cos(ph),
+                    rng.normal(0, 15, n)])
+    ics[2, 70000] = np.nan
+    dt = rng.uniform(1e-4, 1e-2, n)
+    got = gpu_bs23(cfg, obs, ics, dt, 3, 1e-6, 1e-8, precision)
+    for a in range(0, n, 20000):
+        part = gpu_bs23(cfg, obs, np.ascontiguousarray(ics[:, a:a + 20000]), dt[a:a + 20000], 3, 1e-6, 1e-8, precision)
+        for g, p in zip(got, part):
+            assert g[a:a + 20000].tobytes() == p.tobytes(), a
