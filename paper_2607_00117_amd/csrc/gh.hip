@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -105,7 +106,36 @@ __global__ __launch_bounds__(256) void k_fit_copy(const TA* __restrict__ A, int6
 }
 
 // The Gauss-Hermite block of the fit matrix: out[i][h0 + (m - 1) n_ap + a] =
-// g_m(i, a) / gamma[a], m = 1..n_gh.  A workgroup takes kFitOrb orbits x kFitAp
+// g_m(i, a) / gamma[a], m = 1..n_gh, one thread per (orbit, aperture).
+template <typename TA>
+__global__ __launch_bounds__(256) void k_fit_gh_rows(const TA* __restrict__ A, int64_t n_orb, int64_t n_con,
+                                                     int64_t kin0, int32_t n_ap, int32_t nv, int32_t n_gh,
+                                                     const double* __restrict__ G, const double* __restrict__ inv_gamma,
+                                                     int64_t h0, int64_t n_out, TA* __restrict__ out) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n_orb * n_ap) return;
+  const int64_t i = t / n_ap;
+  const int a = (int)(t - i * n_ap);
+  const TA* row = A + i * n_con + kin0 + (int64_t)a * nv;
+  const double* Ga = G + (size_t)a * (n_gh + 1) * nv;
+  double acc[kMaxGH + 1];
+#pragma unroll
+  for (int m = 0; m <= kMaxGH; ++m) acc[m] = 0.0;
+  for (int k = 0; k < nv; ++k) {
+    const double v = (double)row[k];
+    if (v == 0.0) continue;
+#pragma unroll
+    for (int m = 1; m <= kMaxGH; ++m)
+      if (m <= n_gh) acc[m] += Ga[(size_t)m * nv + k] * v;
+  }
+  TA* o = out + i * n_out + h0 + a;
+  const double ig = inv_gamma[a];
+#pragma unroll
+  for (int m = 1; m <= kMaxGH; ++m)
+    if (m <= n_gh) o[(int64_t)(m - 1) * n_ap] = (TA)(acc[m] * ig);
+}
+
+// The same by tiles: a workgroup takes kFitOrb orbits x kFitAp
 // apertures, one of each per thread, and walks the bins kFitBins at a time: the
 // rows' segments and the apertures' maps go through LDS, so that both are read in
 // whole lines (a thread that walks its own bins and map touches 5 lines per bin).
@@ -164,6 +194,23 @@ __global__ __launch_bounds__(256) void k_fit_gh(const TA* __restrict__ A, int64_
 #pragma unroll
   for (int m = 0; m < kMaxGH; ++m)
     if (m < n_gh) o[(int64_t)m * n_ap] = (TA)(acc[m] * ig);
+}
+
+static int64_t fit_tiles(int64_t n_orb, int32_t n_ap) {
+  return (n_orb + kFitOrb - 1) / kFitOrb * ((n_ap + kFitAp - 1) / kFitAp);
+}
+
+// Whether the tiles are taken: a thread that walks its own bins costs by the bytes
+// between two threads' bins, a tile by its 16 apertures x 16 bins whether they are
+// used or not, so the used share of a tile times an aperture's bytes decides.
+// A call with four moments, per thread and tiled: 100 apertures x 20 bins of
+// 15,000 FP64 orbits 0.60 and 0.20 ms; 1 x 30 of 400,000 FP32 orbits 0.21 and
+// 0.30; 8 x 8 of 400,000 FP64 orbits 0.16 and 0.22 (28 bytes and 4 apertures are
+// the least for which no size that was measured lost).
+static bool fit_tiled(int64_t n_orb, int32_t n_ap, int32_t nv, size_t bytes) {
+  const auto used = [](double n, double t) { return n / (t * std::ceil(n / t)); };
+  return n_ap >= 4 && used(n_ap, kFitAp) * used(nv, kFitBins) * (double)(nv * bytes) >= 28.0 &&
+         fit_tiles(n_orb, n_ap) < (int64_t)1 << 24;  // 2^32 threads of a launch
 }
 
 }  // namespace sw
@@ -253,20 +300,18 @@ extern "C" int gh_fit_matrix(const void* A, int32_t dtype, int64_t n_orb, int64_
   const int32_t n_sig = surf0 >= 0 ? n_ap : 0;
   const int64_t h0 = n_mass + n_sig, n_out = h0 + (int64_t)n_gh * n_ap;
   const int64_t nc = n_orb * (n_mass + n_sig);
-  const int64_t ng = (n_orb + kFitOrb - 1) / kFitOrb * ((n_ap + kFitAp - 1) / kFitAp);
-  if (dtype == SW_F32) {
+  const bool tiled = fit_tiled(n_orb, n_ap, nv, dtype == SW_F32 ? 4 : 8);
+  const int64_t ng = tiled ? fit_tiles(n_orb, n_ap) : (n_orb * n_ap + 255) / 256;
+  const auto go = [&](auto* a, auto* o) {
+    typedef std::remove_pointer_t<decltype(o)> TA;
     if (nc > 0)
-      hipLaunchKernelGGL(k_fit_copy<float>, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, (const float*)A, n_orb,
-                         n_con, n_mass, surf0, n_sig, n_out, (float*)out);
-    hipLaunchKernelGGL(k_fit_gh<float>, dim3((unsigned)ng), dim3(256), 0, st, (const float*)A, n_orb,
-                       n_con, kin0, n_ap, nv, n_gh, Gd, ig, h0, n_out, (float*)out);
-  } else {
-    if (nc > 0)
-      hipLaunchKernelGGL(k_fit_copy<double>, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, (const double*)A,
-                         n_orb, n_con, n_mass, surf0, n_sig, n_out, (double*)out);
-    hipLaunchKernelGGL(k_fit_gh<double>, dim3((unsigned)ng), dim3(256), 0, st, (const double*)A, n_orb,
-                       n_con, kin0, n_ap, nv, n_gh, Gd, ig, h0, n_out, (double*)out);
-  }
+      hipLaunchKernelGGL(k_fit_copy<TA>, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, a, n_orb, n_con, n_mass,
+                         surf0, n_sig, n_out, o);
+    hipLaunchKernelGGL(tiled ? k_fit_gh<TA> : k_fit_gh_rows<TA>, dim3((unsigned)ng), dim3(256), 0, st, a, n_orb, n_con,
+                       kin0, n_ap, nv, n_gh, Gd, ig, h0, n_out, o);
+  };
+  if (dtype == SW_F32) go((const float*)A, (float*)out);
+  else go((const double*)A, (double*)out);
   SW_HIP(hipGetLastError());
   SW_HIP(hipStreamSynchronize(st));  // the host copy of the maps must outlive the transfer
   return SW_OK;

@@ -149,3 +149,10 @@ def test_bundle_rows_edges(gpu, nb, c, nd, dtype):
     for k in range(1, nd):
         want = want + A[k::nd]
     assert np.array_equal(out.cpu().numpy(), (want / nd).astype(A.dtype))
+
+
+# few apertures or short histograms: a thread per orbit and aperture, workgroups around 256 of them
+@pytest.mark.parametrize("n,n_ap,nv,n_gh", [(257, 1, 33, 8), (85, 3, 60, 4), (31, 17, 5, 1)])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_fit_block_by_threads_equals_the_moments(gpu, n, n_ap, nv, n_gh, dtype):
+    test_fit_block_equals_the_moments(gpu, n, n_ap, nv, n_gh, dtype)
