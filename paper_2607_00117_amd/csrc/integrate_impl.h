@@ -255,17 +255,17 @@ void k_integrate(const PotK p0, const sw_potential* __restrict__ pots, const int
                                        : *reinterpret_cast<const PotK*>(pots + pot_index(offsets, n_pot, o));
     Leap<T, LPO, NB> L;
     L.start(P, ics, dts[o], n_orb, o, part);
-    const double E0 = energy<T, NB>(P, L.s, L.lamw);
-    double dmax = 0.0;
+    double E0 = 0.0, dmax = 0.0;
+    if constexpr (BIN) E0 = energy<T, NB>(P, L.s, L.lamw);
     const int de = O.drift_every;
     int slot = 0;
     for (int k = 1; k <= n_steps; ++k) {
       L.step(P);
-      if (de > 0 && k % de == 0) {
-        const double e = fabs(energy<T, NB>(P, L.s, L.lamw) / E0 - 1.0);
-        if (!(e <= dmax)) dmax = e;
-      }
       if constexpr (BIN) {
+        if (de > 0 && k % de == 0) {
+          const double e = fabs(energy<T, NB>(P, L.s, L.lamw) / E0 - 1.0);
+          if (!(e <= dmax)) dmax = e;
+        }
         uint32_t mc[4], kc[4];
         cells4<T, CYL>(P, O, L.s, mc, kc);
         if (part == 0) {
@@ -282,8 +282,9 @@ void k_integrate(const PotK p0, const sw_potential* __restrict__ pots, const int
       }
     }
     if (valid && part == 0) {
-      write_checks<T>(L.s, dmax, o, drift, flags);
-      if constexpr (!BIN) {
+      if constexpr (BIN) {
+        write_checks<T>(L.s, dmax, o, drift, flags);
+      } else {
 #pragma unroll
         for (int i = 0; i < 6; ++i) final_state[(int64_t)i * n_orb + o] = L.s[i];
       }
