@@ -30,29 +30,29 @@ template <>
 struct Prec<float> {
   // LPO lanes per orbit: each lane's share, then the sum over the lane group
   // (the same sum in every lane of the group, so their states stay identical)
-  template <int LPO = 1, bool NB = false>
+  template <int LPO = 1, int NB = 0>
   __device__ static void accel(const PotK& P, const float* s, float* g, float& lamw, int part = 0) {
     float gb[3];
-    accel_f32<LPO, NB, true>(P, s[0], s[1], s[2], g[0], g[1], g[2], gb, lamw, part);
+    accel_f32<LPO, NB != 0, true>(P, s[0], s[1], s[2], g[0], g[1], g[2], gb, lamw, part);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       if constexpr (LPO == 2) gb[k] += __shfl_xor(gb[k], 1, 64);
       g[k] += gb[k];
     }
   }
-  template <bool NB = false>
+  template <int NB = 0>
   __device__ static double jacobi(const PotK& P, const double* sd, float lamw) {
-    return jacobi_f64_drift<NB>(P, sd, lamw);
+    return jacobi_f64_drift<NB != 0>(P, sd, lamw);
   }
 };
 template <>
 struct Prec<double> {
-  template <int LPO = 1, bool NB = false>
+  template <int LPO = 1, int NB = 0>
   __device__ static void accel(const PotK& P, const double* s, double* g, float&, int = 0) {
     static_assert(LPO == 1, "the double-precision path runs one lane per orbit");
     accel_f64<NB>(P, s, g);
   }
-  template <bool NB = false>
+  template <int NB = 0>
   __device__ static double jacobi(const PotK& P, const double* sd, float) { return jacobi_f64<NB>(P, sd); }
 };
 
@@ -117,7 +117,7 @@ __device__ __forceinline__ const PotK& tile_pot(const sw_potential* pots, int k)
 }
 
 // One orbit's leapfrog state.
-template <typename T, int LPO, bool NB>
+template <typename T, int LPO, int NB>
 struct Leap {
   T s[6], g[3], dt, h, c, sn, cm1;
   float lamw;
@@ -168,7 +168,7 @@ struct Leap {
   }
 };
 
-template <typename T, bool NB>
+template <typename T, int NB>
 __device__ __forceinline__ double energy(const PotK& P, const T* s, float lamw) {
   double sd[6];
 #pragma unroll
@@ -236,6 +236,7 @@ void k_integrate(const PotK p0, const sw_potential* __restrict__ pots, const int
                  uint64_t* __restrict__ ev_k, double* __restrict__ drift, uint8_t* __restrict__ flags,
                  T* __restrict__ final_state) {
   constexpr int OPW = kWave / LPO;  // orbits per wave
+  constexpr int KB = NB && MODE == kPotOrbit ? 2 : NB;
   constexpr int ST = kStage / 2;
   __shared__ uint64_t staged[kTileWaves][2][ST][OPW + 1];
   const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -253,17 +254,17 @@ void k_integrate(const PotK p0, const sw_potential* __restrict__ pots, const int
     const PotK& P = MODE == kPotOne    ? p0
                     : MODE == kPotTile ? tile_pot(pots, tl.kpot)
                                        : *reinterpret_cast<const PotK*>(pots + pot_index(offsets, n_pot, o));
-    Leap<T, LPO, NB> L;
+    Leap<T, LPO, KB> L;
     L.start(P, ics, dts[o], n_orb, o, part);
     double E0 = 0.0, dmax = 0.0;
-    if constexpr (BIN) E0 = energy<T, NB>(P, L.s, L.lamw);
+    if constexpr (BIN) E0 = energy<T, KB>(P, L.s, L.lamw);
     const int de = O.drift_every;
     int slot = 0;
     for (int k = 1; k <= n_steps; ++k) {
       L.step(P);
       if constexpr (BIN) {
         if (de > 0 && k % de == 0) {
-          const double e = fabs(energy<T, NB>(P, L.s, L.lamw) / E0 - 1.0);
+          const double e = fabs(energy<T, KB>(P, L.s, L.lamw) / E0 - 1.0);
           if (!(e <= dmax)) dmax = e;
         }
         uint32_t mc[4], kc[4];

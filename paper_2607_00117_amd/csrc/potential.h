@@ -177,7 +177,7 @@ __device__ __forceinline__ float asinh_<float>(float v) {
   return v < 0.0f ? -r : r;
 }
 
-template <typename T, int NK, int NG>
+template <typename T, int NK, int NG, bool LANES = false>
 __device__ __forceinline__ void needle_sums(const T* gq, const T* gw, T x, T c, T L, T eta, T* J, T* X) {
 #pragma unroll
   for (int k = 0; k < NK; ++k) { J[k] = T(0); X[k] = T(0); }
@@ -187,17 +187,20 @@ __device__ __forceinline__ void needle_sums(const T* gq, const T* gw, T x, T c, 
     const T ua = asinh_<T>(((h ? -L : T(0)) - x) * ic), ub = asinh_<T>(((h ? T(0) : L) - x) * ic);
     const T du = ub - ua;
     for (int j = 0; j < NG; ++j) {
-      T t, w, e, ie;
+      T t, w, e, ie, q = gq[j], W = gw[j];
+      // both loads of the node before the first use: with few registers left the
+      // compiler sinks the second one and waits for memory twice per node
+      if constexpr (LANES && sizeof(T) == 8) asm volatile("" : "+v"(q), "+v"(W));
       if constexpr (sizeof(T) == 4) {
-        t = rsqf_(1.0f + gq[j]);
+        t = rsqf_(1.0f + q);
         e = __expf(ua + du * t);
         ie = rcpf_(e);
       } else {
-        t = T(1) / sqrt(T(1) + gq[j]);
+        t = T(1) / sqrt(T(1) + q);
         e = exp(ua + du * t);
         ie = T(1) / e;
       }
-      w = T(0.5) * gw[j] * (t * t * t);
+      w = T(0.5) * W * (t * t * t);
       const T sh = T(0.5) * (e - ie), ch = T(0.5) * (e + ie);
       const T s = x + c * sh;
       const T as = s < T(0) ? -s : s;
@@ -242,8 +245,9 @@ __device__ __forceinline__ void needle_coeffs(T a, T b2, T Z, T zeta, T* c, T* d
 }
 
 // potential (phi != null) and acceleration added into g (g != null) of one needle bar;
-// K holds GM, a, b^2, L, eta (C.c or C.f)
-template <typename T, int NT, int NG>
+// K holds GM, a, b^2, L, eta (C.c or C.f); LANES: every lane has a potential, and a
+// quadrature rule in memory, of its own
+template <typename T, int NT, int NG, bool LANES = false>
 __device__ __forceinline__ void needle_bar(const T* K, const T* gq, const T* gw, T x, T y, T z, T* phi, T* g) {
   const T GM = K[0], a = K[1], b2 = K[2], L = K[3], eta = K[4];
   T zeta, c;
@@ -261,7 +265,7 @@ __device__ __forceinline__ void needle_bar(const T* K, const T* gq, const T* gw,
     c = sqrt(y * y + Z * Z);
   }
   T J[NT + 1], X[NT + 1], cf[NT], dcf[NT];
-  needle_sums<T, NT + 1, NG>(gq, gw, x, c, L, eta, J, X);
+  needle_sums<T, NT + 1, NG, LANES>(gq, gw, x, c, L, eta, J, X);
   needle_coeffs<T, NT>(a, b2, Z, zeta, cf, dcf);
   if (phi) {
     T sp = T(0);
@@ -384,9 +388,10 @@ __device__ __forceinline__ void accel_f32(const PotK& P, float x, float y, float
 
 // ---------------------------------------------------------------------------
 // Double-precision acceleration and potential.  The analytic components use
-// exactly the operation order of their defining formulas.
+// exactly the operation order of their defining formulas.  NB: needle bars, 2
+// where every lane has a potential of its own.
 // ---------------------------------------------------------------------------
-template <bool NB = false>
+template <int NB = 0>
 __device__ inline void accel_f64(const PotK& P, const double* xv, double* g) {
   const double x = xv[0], y = xv[1], z = xv[2];
   g[0] = 0.0; g[1] = 0.0; g[2] = 0.0;
@@ -439,10 +444,10 @@ __device__ inline void accel_f64(const PotK& P, const double* xv, double* g) {
         ferrers_f64(C, P.gq64, P.gw64, x, y, z, nullptr, g);
         break;
       case SW_DA_T3:
-        if constexpr (NB) needle_bar<double, 3, kGL64>(C.c, P.gq64, P.gw64, x, y, z, nullptr, g);
+        if constexpr (NB) needle_bar<double, 3, kGL64, NB == 2>(C.c, P.gq64, P.gw64, x, y, z, nullptr, g);
         break;
       case SW_DA_V4:
-        if constexpr (NB) needle_bar<double, 5, kGL64>(C.c, P.gq64, P.gw64, x, y, z, nullptr, g);
+        if constexpr (NB) needle_bar<double, 5, kGL64, NB == 2>(C.c, P.gq64, P.gw64, x, y, z, nullptr, g);
         break;
       default:
         break;
@@ -451,10 +456,11 @@ __device__ inline void accel_f64(const PotK& P, const double* xv, double* g) {
 }
 
 // potential of a needle bar in double precision (32-node rule per half)
+template <bool LANES = false>
 __device__ inline double needle_phi_f64(const PotK& P, const CompK& C, double x, double y, double z) {
   double v = 0.0;
-  if (C.kind == SW_DA_T3) needle_bar<double, 3, kGL64>(C.c, P.gq64, P.gw64, x, y, z, &v, nullptr);
-  else needle_bar<double, 5, kGL64>(C.c, P.gq64, P.gw64, x, y, z, &v, nullptr);
+  if (C.kind == SW_DA_T3) needle_bar<double, 3, kGL64, LANES>(C.c, P.gq64, P.gw64, x, y, z, &v, nullptr);
+  else needle_bar<double, 5, kGL64, LANES>(C.c, P.gq64, P.gw64, x, y, z, &v, nullptr);
   return v;
 }
 
@@ -495,7 +501,7 @@ __device__ inline double phi_analytic_f64(const CompK& C, double x, double y, do
   return v;
 }
 
-template <bool NB = false>
+template <int NB = 0>
 __device__ inline double phi_f64(const PotK& P, const double* xv) {
   const double x = xv[0], y = xv[1], z = xv[2];
   double s = 0.0;
@@ -504,7 +510,7 @@ __device__ inline double phi_f64(const PotK& P, const double* xv) {
     double v = 0.0;
     if (C.kind == SW_FERRERS2) ferrers_f64(C, P.gq64, P.gw64, x, y, z, &v, nullptr);
     else if (C.kind == SW_DA_T3 || C.kind == SW_DA_V4) {
-      if constexpr (NB) v = needle_phi_f64(P, C, x, y, z);
+      if constexpr (NB) v = needle_phi_f64<NB == 2>(P, C, x, y, z);
     } else v = phi_analytic_f64(C, x, y, z);
     s = s + v;
   }
@@ -512,7 +518,7 @@ __device__ inline double phi_f64(const PotK& P, const double* xv) {
 }
 
 // E_J = |p|^2/2 + Phi(x) - Omega (x p_y - y p_x)
-template <bool NB = false>
+template <int NB = 0>
 __device__ inline double jacobi_f64(const PotK& P, const double* s6) {
   double kin = 0.5 * (s6[3] * s6[3] + s6[4] * s6[4] + s6[5] * s6[5]);
   double Lz = s6[0] * s6[4] - s6[1] * s6[3];

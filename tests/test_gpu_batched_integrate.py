@@ -280,3 +280,33 @@ def test_waves_sharing_a_tile_give_the_bits_of_one_wave(gpu, offsets, n_steps, e
             alone = _gpu_batched([pot], [0, b - a], ics[:, a:b], dt[a:b], n_steps, obs, dtype)
             for g, r in zip(got, alone):
                 assert g[a:b].tobytes() == r.tobytes()
+
+
+# more tiles than three waves share, as one potential and as ragged ones with tiles of their own; 45 potentials of 88
+# orbits, one per lane; cylindrical grids and needle bars throughout
+@pytest.mark.parametrize("offsets", [[0, 33000], [0, 20011, 33100], list(range(0, 45 * 88 + 1, 88))])
+@pytest.mark.parametrize("grid", ["cartesian", "cylindrical"])
+@pytest.mark.parametrize("needle", [False, True])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_every_form_gives_the_bits_of_one_wave(gpu, offsets, grid, needle, dtype):
+    from tests.test_gpu_needle import COMPS, _ics as needle_ics
+    P = lib()
+    n_steps = 9
+    if needle:
+        ics, dt = needle_ics(offsets[-1], 9)
+        fams = [(COMPS, (0.3, 0.9, 0.1)), (COMPS[:2], (0.6, 1.0, 0.2))]
+    else:
+        ics, dt = _ics(offsets[-1], seed=7)
+        fams = FP64_POTS[:1] + [([("mn", (4e10, 3.0, 0.3)), ("ferrers2", (1e10, 4.0, 1.5, 1.0))], (0.3, 0.9, 0.1))]
+    pots = [P.build_potential(fams[i % 2][0], 40.0 + i, fams[i % 2][1]) for i in range(len(offsets) - 1)]
+    obs = dict(W.SMALL["obs"] if grid == "cartesian" else CYL, nx=5, nz=4, npx=5, npy=4, nv=5, drift_every=2)
+    got = _gpu_batched(pots, offsets, ics, dt, n_steps, obs, dtype)
+    with _Tuning(integrate_waves_per_cu=8):
+        ref = _gpu_batched(pots, offsets, ics, dt, n_steps, obs, dtype)
+    for g, r in zip(got, ref):
+        assert g.tobytes() == r.tobytes()
+    for k in range(min(len(pots), 3)):  # and of each potential alone
+        a, b = offsets[k], offsets[k + 1]
+        alone = _gpu_batched([pots[k]], [0, b - a], ics[:, a:b], dt[a:b], n_steps, obs, dtype)
+        for g, r in zip(got, alone):
+            assert g[a:b].tobytes() == r.tobytes()
