@@ -538,9 +538,8 @@ int gh_fit_matrix(const void* A, int32_t dtype, int64_t n_orb, int64_t n_con, in
  *   "integrate_lanes_per_orbit" 1, or 2: two lanes share each orbit of the
  *                             single-precision binned integration (each takes
  *                             half of the bar's quadrature nodes)
- *   "hist_lds_kb"             LDS budget (KiB, 4..160) of one histogram
- *                             workgroup that carries several orbit rows (at
- *                             most 16 KiB are used for that)
+ *   "hist_lds_kb"             LDS budget (KiB, 4..160, default 16) of one histogram
+ *                             workgroup; sets how many orbit rows it carries
  *   "sparse_rows_per_wg"      orbit rows per row-dot workgroup of the weight
  *                             solve's compressed passes (0: automatic, else a
  *                             multiple of 16 up to 512)

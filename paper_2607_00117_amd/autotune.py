@@ -1,11 +1,13 @@
 """Autotuner of the integration launch parameters.
 
 Times integrate_and_bin on a sample of the workload for each candidate of
-  integrate_waves_per_cu (0 = one wave per 64-orbit tile, k = persistent grid
-  of k waves per CU), integrate_lanes_per_orbit (1 or 2 lanes share an orbit's
-  force evaluation) and hist_lds_kb (LDS budget of a histogram workgroup),
+  integrate_waves_per_cu (0 = one wave per 64-orbit tile, or two or three that
+  share it, by the number of tiles; k = persistent grid of k waves per CU),
+  integrate_lanes_per_orbit (1 or 2 lanes share an orbit's force evaluation)
+  and hist_lds_kb (LDS budget of a histogram workgroup),
 keeps the fastest, and caches it per workload shape in a JSON file
-($SCHW_TUNE_CACHE, default ~/.cache/schw_tune.json).
+($SCHW_TUNE_CACHE, default ~/.cache/schw_tune.json).  A cached choice counts
+only if it was made among the present budgets.
 """
 import json
 import os
@@ -15,7 +17,7 @@ from . import _lib as P
 
 CANDIDATES_WAVES = (0, 2, 4, 8)
 CANDIDATES_LANES = (1, 2)
-CANDIDATES_LDS = (32, 64, 128)
+CANDIDATES_LDS = (16, 32, 64)
 
 
 def cache_path():
@@ -44,7 +46,7 @@ def tune(run, key, repeats=2, log=None):
     """run(): one integrate_and_bin call on the sample (synchronised by the caller's
     torch.cuda.synchronize inside).  Returns the best configuration and the table."""
     cache = load_cache()
-    if key in cache:
+    if key in cache and {r["hist_lds_kb"] for r in cache[key]["table"]} == set(CANDIDATES_LDS):
         apply(cache[key]["best"])
         return cache[key]["best"], cache[key]["table"]
     table = []

@@ -17,12 +17,11 @@
 namespace sw {
 
 constexpr int64_t kHistGroups = 2048;  // histogram workgroups wanted before a workgroup takes several rows
-constexpr int64_t kHistLds = 16 * 1024;  // LDS of a histogram workgroup that carries several rows
 constexpr size_t kHistWide = 32 * 1024;  // LDS above which a histogram workgroup takes 512 threads
                                           // (36 and 60 KB rows: 6.1 ms with 256 threads, 5.1 with 512, 5.4 with 1,024)
 
 int g_waves_per_cu = 0;
-int g_hist_lds_kb = 64;
+int g_hist_lds_kb = 16;
 int g_lanes_per_orbit = 1;
 int g_num_cus = 256;
 
@@ -289,8 +288,9 @@ static int launch_hist(const uint64_t* ev, int64_t n_chunk, int32_t n_steps, int
   const int wide = (int64_t)ncopy * n_steps > 65535 ? 1 : 0;
   const int nw = hist_words(ncell, wide);
   // small histograms: rows per workgroup that leave several workgroups per CU (512,000
-  // rows of 1,750 cells: 930 us per block with 64 KB, 281 with 16) and enough workgroups
-  int64_t opw = std::min<int64_t>(g_hist_lds_kb * 1024, kHistLds) / (4 * nw);
+  // rows of 1,750 cells: 930 us per block with a budget of 64 KB, 281 with 16) and
+  // enough workgroups
+  int64_t opw = (int64_t)g_hist_lds_kb * 1024 / (4 * nw);
   opw = std::min<int64_t>(opw, (n_chunk + kHistGroups - 1) / kHistGroups);
   opw = std::max<int64_t>(1, std::min<int64_t>(opw, 32));
   const size_t lds = (size_t)opw * nw * 4;

@@ -220,3 +220,23 @@ def test_tuning_knobs():
 def test_mlp_param_count_matches_architecture():
     assert P.mlp_param_count() == 256 * 12 + 256 + 2 * (256 * 256 + 256) + 256 + 1
     assert P.mlp_workspace_bytes(0) == 0
+
+
+def test_autotuner_leaves_a_choice_among_other_budgets(tmp_path, monkeypatch):
+    """A choice cached when other histogram budgets were tried is made again; one among the present budgets is kept."""
+    import json
+    from paper_2607_00117_amd import autotune
+    monkeypatch.setenv("SCHW_TUNE_CACHE", str(tmp_path / "tune.json"))
+    keys = ("integrate_waves_per_cu", "integrate_lanes_per_orbit", "hist_lds_kb")
+    old = {k: P.get_tuning(k) for k in keys}
+    stale = {"integrate_waves_per_cu": 0, "integrate_lanes_per_orbit": 1, "hist_lds_kb": 128}
+    (tmp_path / "tune.json").write_text(json.dumps({"shape": {"best": stale, "table": [dict(stale, ms=1.0)]}}))
+    runs = []
+    try:
+        best, table = autotune.tune(lambda: runs.append(1), "shape", repeats=1)
+        assert len(table) == 24 and len(runs) == 48
+        assert best["hist_lds_kb"] in autotune.CANDIDATES_LDS == tuple(sorted({r["hist_lds_kb"] for r in table}))
+        assert autotune.tune(lambda: runs.append(1), "shape", repeats=1) == (best, table) and len(runs) == 48
+    finally:
+        for k, v in old.items():
+            P.set_tuning(k, v)

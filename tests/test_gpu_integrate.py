@@ -138,6 +138,29 @@ def test_histograms_of_several_rows(gpu, n, nx, nz, nv, surface):
     assert np.allclose(np.rint(k)[:, :nx * 5 * nz].sum(1) + ov32[:, 0] * 4 * n_steps, 4 * n_steps, atol=1e-9)
 
 
+@pytest.mark.parametrize("n,n_steps", [(4100, 16400), (6200, 12)])
+@pytest.mark.parametrize("lds_kb", [4, 16, 160])
+def test_histogram_budget(gpu, n, n_steps, lds_kb):
+    """Two to four rows per histogram workgroup (one per 2,048 orbits, as the LDS budget allows), with 32-bit counters
+    (more than 65,535 events) and 16-bit ones: the rows are those of workgroups of one row, which 2,000 orbits at a time
+    take, to the bit."""
+    P = lib()
+    obs = dict(W.SMALL["obs"], nx=7, ny=5, nz=3, npx=7, npy=3, nv=9, drift_every=0)
+    ics, dt = W.grid_ics(W.load_table("plummer_mn"), seed=4, n_steps=1000)
+    rep = -(-n // ics.shape[1])
+    ics, dt = np.tile(ics, rep)[:, :n] * np.linspace(0.9, 1.1, n), np.tile(dt, rep)[:n]
+    old = P.get_tuning("hist_lds_kb")
+    P.set_tuning("hist_lds_kb", lds_kb)
+    try:
+        A, ov, _, _ = gpu_integrate(W.SMALL, ics, dt, n_steps, "f32", obs=obs)
+        for a in range(0, n, 2000):
+            A1, ov1, _, _ = gpu_integrate(W.SMALL, ics[:, a:a + 2000], dt[a:a + 2000], n_steps, "f32", obs=obs)
+            assert np.array_equal(A[a:a + 2000], A1) and np.array_equal(ov[a:a + 2000], ov1)
+    finally:
+        P.set_tuning("hist_lds_kb", old)
+    assert A.max() > 0
+
+
 @pytest.mark.parametrize("lanes", [1, 2])
 def test_barred_fp32_subsample_vs_fp64_oracle(gpu, lanes):
     """Barred model (MN + Ferrers + flattened NFW, 40 km/s/kpc) in FP32 against the
