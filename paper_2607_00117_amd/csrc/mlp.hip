@@ -435,8 +435,13 @@ extern "C" int mlp_infer_bf16(const void* packed, const float* x, int64_t B, flo
   SW_CHECK(packed && x && y, "mlp_infer_bf16: null argument");
   SW_CHECK(B >= 0, "mlp_infer_bf16: bad batch");
   if (B == 0) return SW_OK;
-  hipLaunchKernelGGL(k_mlp_infer_bf16, dim3((unsigned)((B + kRows - 1) / kRows)), dim3(kThr), 0,
-                     (hipStream_t)stream, (const __bf16*)packed, x, B, y);
-  SW_HIP(hipGetLastError());
+  // a launch of 2^32 threads or more (32 a sample) would start their number modulo 2^32
+  constexpr int64_t kPer = (int64_t)1 << 26;
+  for (int64_t b = 0; b < B; b += kPer) {
+    const int64_t n = B - b < kPer ? B - b : kPer;
+    hipLaunchKernelGGL(k_mlp_infer_bf16, dim3((unsigned)((n + kRows - 1) / kRows)), dim3(kThr), 0,
+                       (hipStream_t)stream, (const __bf16*)packed, x + b * kIn, n, y + b);
+    SW_HIP(hipGetLastError());
+  }
   return SW_OK;
 }

@@ -137,6 +137,24 @@ def test_bf16_inference_batch_edges(gpu, B, shift):
     assert np.max(np.abs(y.cpu().numpy() - y_o)) <= 5e-5 * max(1.0, np.abs(y_o).max())
 
 
+def test_infer_batches_beyond_one_launch(gpu):
+    """2^27 + 3 samples, at 32 threads a sample more than the 2^32 threads of a launch: every prediction is written, and
+    those around the launches' bounds and at the ends are those of a small batch."""
+    import torch
+    P = lib()
+    packed = torch.empty(P.mlp_param_count(), dtype=torch.bfloat16, device="cuda")
+    P.mlp_pack_bf16(_dev(L.init(6)), packed)
+    B = 2 ** 27 + 3
+    x = torch.rand((B, 12), device="cuda", generator=torch.Generator(device="cuda").manual_seed(2))
+    y = torch.full((B,), float("nan"), device="cuda")
+    P.mlp_infer_bf16(packed, x, y)
+    assert int(torch.isnan(y).sum()) == 0
+    for a in (0, 2 ** 26 - 16, 2 ** 26, 2 ** 27 - 16, 2 ** 27, B - 16):
+        z = torch.empty(min(16, B - a), device="cuda")
+        P.mlp_infer_bf16(packed, x[a:a + 16].contiguous(), z)
+        assert torch.equal(z, y[a:a + 16]), a
+
+
 def test_training_lowers_loss(gpu):
     import torch
     P = lib()
