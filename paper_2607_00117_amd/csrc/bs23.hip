@@ -392,7 +392,8 @@ bool shares_tile(int64_t tiles, int32_t n_steps, bool f64) {
 
 size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// rows that leave one workgroup per CU take 1,024 threads, shorter ones 256
+// rows that leave one workgroup per CU take 1,024 threads, shorter ones 256 (and
+// launches that 1,024 a row would bring to 2^32 threads)
 int hist_w(const uint64_t* ev_m, const uint64_t* ev_k, const double* wts, const double* ttot, int64_t n, int32_t S,
            const ObsK& O, int64_t n_con, double* A, double* overflow, double upsilon, hipStream_t st) {
   const int32_t nv = O.surface ? O.nv : 0;
@@ -403,7 +404,7 @@ int hist_w(const uint64_t* ev_m, const uint64_t* ev_k, const double* wts, const 
       hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(nt), lds, st, ev_m, ev_k, wts, ttot, S, O.ncopy, O.n_mass,
                          O.n_kin, nv, (int32_t)w0, wn, n_con, A, overflow, upsilon);
     };
-    if (lds > 64 * 1024) go(k_hist_w<1024>, 1024);
+    if (lds > 64 * 1024 && n < (int64_t)1 << 22) go(k_hist_w<1024>, 1024);
     else go(k_hist_w<256>, 256);
     SW_HIP(hipGetLastError());
   }

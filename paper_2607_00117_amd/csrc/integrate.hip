@@ -292,7 +292,8 @@ static int launch_hist(const uint64_t* ev, int64_t n_chunk, int32_t n_steps, int
   // enough workgroups
   int64_t opw = (int64_t)g_hist_lds_kb * 1024 / (4 * nw);
   opw = std::min<int64_t>(opw, (n_chunk + kHistGroups - 1) / kHistGroups);
-  opw = std::max<int64_t>(1, std::min<int64_t>(opw, 32));
+  // at least as many as keep the launch below 2^32 threads
+  opw = std::min<int64_t>(std::max<int64_t>((n_chunk >> 23) + 1, opw), 32);
   const size_t lds = (size_t)opw * nw * 4;
   if (lds > 160 * 1024) {
     set_error("integrate_and_bin: block of %d cells does not fit the LDS histogram", ncell);
