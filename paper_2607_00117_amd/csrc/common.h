@@ -92,6 +92,13 @@ extern int g_sparse_cols;
 extern int g_sparse_lanes;
 extern int g_rhs_group;
 
+// A wave's own LDS exchange: writes before, reads after, no other wave involved.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace sw
 
 #define SW_HIP(call)                                              \

@@ -678,6 +678,7 @@ __global__ __launch_bounds__(kPotrfThreads) void k_potrf_diag(float* __restrict_
         const float l = i > k ? a[k] * ip : 0.0f;
         a[k] = i > k ? l : (i == k ? piv : a[k]);
         Lt[k][i] = a[k];  // the other rows' entries come back as broadcasts (both halves of the wave write the same)
+        wave_fence();
         if (k + 1 < kPan) {
           a[k + 1] -= l * lane_float(l, k + 1);
           pivot(k + 1);  // its chain runs beside the step's other updates

@@ -210,13 +210,6 @@ __device__ __forceinline__ void write_stage(const uint64_t (*stm)[OPW + 1], cons
   }
 }
 
-// A wave's own LDS exchange: writes before, reads after, no other wave involved.
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // One wave does all of a tile's work; a workgroup carries up to kTileWaves tiles,
 // which share nothing: the waves of a workgroup are spread over the SIMDs of its
 // CU, while workgroups of one wave may meet on one SIMD with others idle (the
