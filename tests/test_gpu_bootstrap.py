@@ -131,6 +131,34 @@ def test_dense_passes_in_every_tile_height(gpu, dtype):
     assert np.abs(out[8][0] - w_o).sum() / np.abs(w_o).sum() < W_L1_TOL
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_dense_passes_every_vector(gpu, dtype):
+    """Every vector of the dense passes, not the first rows of their tiles alone: each tile height's weights are those of
+    128 vectors to the bit, vectors at the bounds of the 16-row blocks agree with the oracle, and 129 and 150 vectors (two
+    tiles each) agree with the 128 and, past them, with the oracle (both sides within its bar)."""
+    P = lib()
+    n, c, cb = 530, 201, 70
+    blocks = [(0, cb), (cb, c)]
+    A = W.sparse_lognormal_matrix(n, blocks, density=0.3, seed=6).astype(dtype)
+    d, sig, wt = mock_problem(A, blocks, 4, 0.02, 0.02)
+    D = BS.bootstrap_data(d, sig, W.bootstrap_eps(150, c, seed=1), cb, c)
+    old = P.get_tuning("multi_dense")
+    P.set_tuning("multi_dense", 1)
+    try:
+        out = {m: multi_solve(A, D[:m], sig, wt)[0] for m in (15, 16, 17, 33, 64, 65, 81, 97, 112, 113, 128, 129, 150)}
+    finally:
+        P.set_tuning("multi_dense", old)
+    for m in out:
+        if m <= 128:
+            assert np.array_equal(out[m], out[128][:m]), m
+        else:
+            assert out[m].shape[0] == m
+            assert (np.abs(out[m][:128] - out[128]).sum(1) < 2 * W_L1_TOL * np.abs(out[128]).sum(1)).all()
+    for k, m in ((15, 128), (16, 128), (63, 128), (112, 128), (127, 128), (128, 129), (75, 150), (128, 150), (149, 150)):
+        w_o, _ = oracle_solve(A, D[k], sig, wt, 1e-2)
+        assert np.abs(out[m][k] - w_o).sum() / np.abs(w_o).sum() < W_L1_TOL, (k, m)
+
+
 def test_multi_rhs_agrees_with_separate_solves_dense_and_masked(gpu):
     """Dense matrix (uncompressed passes) and masked orbits: each realisation
     agrees with its own solve_weights call."""
