@@ -531,10 +531,15 @@ int gh_fit_matrix(const void* A, int32_t dtype, int64_t n_orb, int64_t n_con, in
 
 /* ---------------------------------------------------------------------------
  * Launch tuning (process-wide, not thread-safe; set before launching work):
- *   "integrate_waves_per_cu"  0: one workgroup per 64-orbit tile, of one wave or
- *                             of two or three that share the tile's work; k in
- *                             [1, 64] (one wave per tile): persistent grid of k waves
- *                             per compute unit walking the orbit tiles
+ *   "integrate_waves_per_cu"  0: by the number of 64-orbit tiles.  Binned launches
+ *                             of up to two tiles per compute unit give a tile
+ *                             three waves that share its work, larger ones in
+ *                             single precision two (one with needle bars), the
+ *                             others, integrate_orbits and launches of many
+ *                             small potentials one; workgroups of one-wave tiles
+ *                             hold one to four of them.  k in [1, 64]: persistent
+ *                             grid of k waves per compute unit walking the orbit
+ *                             tiles, one wave per tile
  *   "integrate_lanes_per_orbit" 1, or 2: two lanes share each orbit of the
  *                             single-precision binned integration (each takes
  *                             half of the bar's quadrature nodes)

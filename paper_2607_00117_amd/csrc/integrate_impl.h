@@ -3,10 +3,10 @@
 // kick-drift-kick leapfrog in the corotating bar frame, keeps the force of the
 // last kick for the next step's first kick, bins the four mirror copies of
 // every synchronised state and stages the packed cell indices of
-// kStage steps in LDS.  The wave then writes each orbit's staged steps as one
-// contiguous 128-byte segment of that orbit's event stream (64 bytes where two
-// waves share a tile), so the stream is written with full-line stores although
-// each lane owns a different orbit.  Bound by the serial chain of a step: up to
+// up to kStage steps in LDS.  The wave then writes each orbit's staged steps as
+// one contiguous segment of that orbit's event stream (128 bytes where three
+// waves share a tile, else 64), so that lanes that own different orbits store
+// whole runs of bytes.  Bound by the serial chain of a step: up to
 // one wave per SIMD, its latency; above, the issue of its ~1,300 instructions.
 //
 // Event word (uint64, one per orbit per step per block): four 16-bit cell
@@ -215,7 +215,11 @@ __device__ __forceinline__ void write_stage(const uint64_t (*stm)[OPW + 1], cons
 // CU, while workgroups of one wave may meet on one SIMD with others idle (the
 // barred model in FP64, 300 steps, 1,024 tiles: 8.3 ms in workgroups of one
 // tile, 5.1 of four).  At most 168 registers, so that three waves share a SIMD (the default
-// allocation lands one register above that, at two waves); no spills.
+// allocation lands one register above that, at two waves).  In FP64, and with
+// needle bars, more are live than that and 2 to 86 of them go to scratch, most of
+// them constants of the binning that a step reloads once: 100,000 FP64 orbits of
+// the barred model x 100 steps take 4.7 ms, on a cylindrical grid (42 spilled) 4.9;
+// binning one copy after the other (none and 12 spilled) they took 5.1 both.
 //
 // LPO lanes per orbit (1, or 2 in single precision): a wave carries 64 / LPO
 // orbits; the lanes of a pair hold the same state, each evaluates its share of
@@ -400,7 +404,8 @@ struct IntegrateLaunch {
 };
 
 // Process-wide launch knobs (set through sw_set_tuning):
-//  g_waves_per_cu  0: one wave per 64-orbit tile; k > 0: persistent grid of k waves per CU
+//  g_waves_per_cu  0: a tile of 64 orbits to one wave (one to four such tiles per workgroup) or to a workgroup of
+//                  two or three waves (below); k > 0: persistent grid of k waves per CU, one wave per tile
 //  g_hist_lds_kb   LDS budget of one histogram workgroup (orbits per workgroup follow)
 extern int g_waves_per_cu;
 extern int g_hist_lds_kb;

@@ -21,6 +21,8 @@ __device__ __forceinline__ float rsqf_(float x) { return __builtin_amdgcn_rsqf(x
 // check are compiled into several kernels that must agree on every bit (an orbit's
 // histogram does not survive a rounding difference), and which product of a b + c d
 // the compiler fuses changes with the code around it: contractions are written out.
+// (The needle bars' sums are left to the compiler: the forms of the leapfrog launch
+// agree on their bits as it builds them, which the tests check.)
 // F: the leapfrog integrator; the adaptive one runs without.
 template <bool F>
 __device__ __forceinline__ float mad_(float a, float b, float c) {

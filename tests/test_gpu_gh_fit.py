@@ -134,7 +134,7 @@ def test_fit_block_equals_the_moments(gpu, n, n_ap, nv, n_gh, dtype):
     assert np.array_equal(F[:, n_mass:n_mass + n_ap], At[:, surf0:], equal_nan=True)
 
 
-# columns around the 256-thread and 1,024-entry steps of the bundling kernel, rows per bundle around its four loads
+# outputs around the 256 threads of the bundling kernel's workgroups, one to nine rows per bundle
 @pytest.mark.parametrize("nb,c,nd", [(1, 1, 1), (3, 255, 2), (7, 256, 3), (5, 257, 4), (300, 7, 5), (2, 1025, 8), (3, 3001, 9)])
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 def test_bundle_rows_edges(gpu, nb, c, nd, dtype):
