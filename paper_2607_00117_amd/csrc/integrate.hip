@@ -40,7 +40,9 @@ __device__ __forceinline__ double div_whole(double a, double b, double r) {
 // a wave whose cells are all empty (nine in ten cells are) writes zeros without
 // arithmetic.  100,000 orbits x 10,000 steps into 18,000 + 30,000 cells: 19.2 ms
 // before, 10.2 now (3.5 TB/s).
-constexpr int kEv = 8;
+// Rows of few events leave most threads of a workgroup without one: with WAVE each
+// wave takes rows of its own (400,000 rows of 8 events: 374 us with all threads on a
+// row and kEv = 8, 338 with kEv = 1, 154 with a wave per row).
 
 template <typename T> struct RowRun;  // the cells of one lane's store (16 bytes, aligned like T)
 template <> struct RowRun<float> {
@@ -55,7 +57,7 @@ __host__ __device__ inline int32_t hist_words(int32_t ncell, int32_t wide) {
   return ((wide ? ncell : (ncell + 1) >> 1) + 3) & ~3;
 }
 
-template <typename T, int NT>
+template <typename T, int NT, int kEv, bool WAVE = false>
 __global__ __launch_bounds__(NT) void k_hist(const uint64_t* __restrict__ ev, int64_t n_chunk, int32_t n_steps,
                                              int32_t ncopy, int32_t ncell, int32_t opw, int32_t wide, int64_t row0,
                                              int64_t n_con, int32_t col_off, T* __restrict__ A,
@@ -63,24 +65,25 @@ __global__ __launch_bounds__(NT) void k_hist(const uint64_t* __restrict__ ev, in
                                              int32_t fold_nkin, double div) {
   extern __shared__ __attribute__((aligned(16))) uint32_t hist[];
   __shared__ uint32_t ovc[32];
-  const int tid = threadIdx.x;
+  constexpr int TPR = WAVE ? 64 : NT;  // threads per row
+  const int tid = threadIdx.x, lane = WAVE ? tid & 63 : tid, g0 = WAVE ? tid >> 6 : 0;
   const int nw = hist_words(ncell, wide);
   const int64_t j0 = (int64_t)blockIdx.x * opw;
   const int no = (int)(n_chunk - j0 < opw ? n_chunk - j0 : opw);  // orbits of this workgroup
   for (int i = tid; i < no * nw / 4; i += NT) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
   if (tid < 32) ovc[tid] = 0u;
   __syncthreads();
-  for (int g = 0; g < no; ++g) {
+  for (int g = g0; g < no; g += NT / TPR) {
     const uint64_t* e = ev + (j0 + g) * (int64_t)n_steps;
     uint32_t* hg = hist + g * nw;
     uint32_t ov = 0;
-    for (int s0 = tid; s0 < n_steps; s0 += kEv * NT) {
+    for (int s0 = lane; s0 < n_steps; s0 += kEv * TPR) {
       uint64_t v[kEv];
 #pragma unroll
-      for (int u = 0; u < kEv; ++u) v[u] = __builtin_nontemporal_load(e + (s0 + u * NT < n_steps ? s0 + u * NT : s0));
+      for (int u = 0; u < kEv; ++u) v[u] = __builtin_nontemporal_load(e + (s0 + u * TPR < n_steps ? s0 + u * TPR : s0));
 #pragma unroll
       for (int u = 0; u < kEv; ++u) {
-        if (s0 + u * NT >= n_steps) break;
+        if (s0 + u * TPR >= n_steps) break;
         for (int c = 0; c < ncopy; ++c) {
           uint32_t idx = (uint32_t)(v[u] >> (16 * c)) & 0xFFFFu;
           // surface pass: kinematic codes ap*nv + v_bin and n_kin + ap fold to ap
@@ -104,10 +107,10 @@ __global__ __launch_bounds__(NT) void k_hist(const uint64_t* __restrict__ ev, in
   constexpr int RW = 16 / sizeof(T);  // cells per store
   typedef typename RowRun<T>::type run;
   const double denom = (double)ncopy * (double)n_steps, inv = 1.0 / denom;
-  for (int g = 0; g < no; ++g) {
+  for (int g = g0; g < no; g += NT / TPR) {
     const uint32_t* hg = hist + g * nw;
     T* row = A + (row0 + j0 + g) * n_con + col_off;
-    for (int c = tid * RW; c < ncell; c += NT * RW) {
+    for (int c = lane * RW; c < ncell; c += TPR * RW) {
       uint32_t cnt[RW];
       if (wide) {
 #pragma unroll
@@ -141,7 +144,7 @@ __global__ __launch_bounds__(NT) void k_hist(const uint64_t* __restrict__ ev, in
           if (c + k < ncell) row[c + k] = v[k];
       }
     }
-    if (tid == 0 && slot >= 0) overflow[(row0 + j0 + g) * 2 + slot] = (double)ovc[g] / denom;
+    if (lane == 0 && slot >= 0) overflow[(row0 + j0 + g) * 2 + slot] = (double)ovc[g] / denom;
   }
 }
 
@@ -304,8 +307,12 @@ static int launch_hist(const uint64_t* ev, int64_t n_chunk, int32_t n_steps, int
     hipLaunchKernelGGL(kernel, grid, dim3(nt), lds, st, ev, n_chunk, n_steps, ncopy, ncell, (int32_t)opw, wide, row0,
                        n_con, col_off, (T*)A, overflow, slot, fold_nv, fold_nkin, div);
   };
-  if (lds > kHistWide) go(k_hist<T, 512>, 512);
-  else go(k_hist<T, 256>, 256);
+  // a thread of 256 has one event at most up to 256 steps; waves of their own pay
+  // while a row is one or two events per lane and there are rows for all four
+  if (lds > kHistWide) go(k_hist<T, 512, 8>, 512);
+  else if (n_steps <= 128 && opw >= 4) go(k_hist<T, 256, 1, true>, 256);
+  else if (n_steps <= 256) go(k_hist<T, 256, 1>, 256);
+  else go(k_hist<T, 256, 8>, 256);
   SW_HIP(hipGetLastError());
   return SW_OK;
 }

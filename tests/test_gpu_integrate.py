@@ -161,6 +161,24 @@ def test_histogram_budget(gpu, n, n_steps, lds_kb):
     assert A.max() > 0
 
 
+@pytest.mark.parametrize("n_steps", [1, 63, 64, 65, 128, 129, 256, 257])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_histograms_of_few_events(gpu, dtype, n_steps):
+    """Rows of a few events: five rows per workgroup (8,300 orbits), a wave to each up to 128 steps and all threads on one
+    above, one load per thread up to 256 steps and eight above, against workgroups of one row (2,000 orbits at a time),
+    with the surface block, to the bit."""
+    obs = dict(W.SMALL["obs"], nx=7, ny=5, nz=3, npx=7, npy=3, nv=9, drift_every=0, surface=1, upsilon=2.5)
+    n = 8300
+    ics, dt = W.grid_ics(W.load_table("plummer_mn"), seed=4, n_steps=1000)
+    rep = -(-n // ics.shape[1])
+    ics, dt = np.tile(ics, rep)[:, :n] * np.linspace(0.9, 1.1, n), np.tile(dt, rep)[:n]
+    A, ov, _, _ = gpu_integrate(W.SMALL, ics, dt, n_steps, dtype, obs=obs)
+    for a in range(0, n, 2000):
+        A1, ov1, _, _ = gpu_integrate(W.SMALL, ics[:, a:a + 2000], dt[a:a + 2000], n_steps, dtype, obs=obs)
+        assert np.array_equal(A[a:a + 2000], A1) and np.array_equal(ov[a:a + 2000], ov1)
+    assert A.max() > 0
+
+
 @pytest.mark.parametrize("lanes", [1, 2])
 def test_barred_fp32_subsample_vs_fp64_oracle(gpu, lanes):
     """Barred model (MN + Ferrers + flattened NFW, 40 km/s/kpc) in FP32 against the
