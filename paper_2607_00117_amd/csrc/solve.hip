@@ -3273,13 +3273,16 @@ static hipError_t wcolsum(const void* A, int32_t dtype, int64_t n_orb, int64_t n
   return hipGetLastError();
 }
 
-// rows per slab: enough slabs for about 1,024 workgroups, at least 32 rows each
-// (a slab's rows are read eight at a time; shorter slabs only add partials to
-// sum), at most max_slabs
-static int64_t slab_rows(int32_t dtype, int64_t n_orb, int64_t ncol, int max_slabs) {
+// rows per slab: enough slabs for about 1,024 workgroups, at most max_slabs, at
+// least `least` rows each (a slab's rows are read eight at a time, one batch after
+// the other).  chi^2 takes 32: shorter slabs only add partials to sum.  Sums that
+// are added in place take 16, and 8 where there are few rows: 500 x 1,750 FP32
+// 27 us with 32 rows, 23 with 16, 22 with 8; 2,000 x 200 22, 23 and 26; 26 x 1,045
+// 25, 23 and 21 (21 with a row per slab and no list of the rows).
+static int64_t slab_rows(int32_t dtype, int64_t n_orb, int64_t ncol, int max_slabs, int64_t least) {
   const int64_t tile = (int64_t)kWsThreads * (dtype == SW_F32 ? RowQuad<float>::n : RowQuad<double>::n);
   const int64_t want = std::min<int64_t>(max_slabs, std::max<int64_t>(1, 1024 * tile / std::max<int64_t>(ncol, 1)));
-  return std::max<int64_t>(32, (n_orb + want - 1) / want);
+  return std::max<int64_t>(least, (n_orb + want - 1) / want);
 }
 
 // chi^2 of Eq. 5 over [cb, ce) with its scratch at `ws` (slabs x C partial
@@ -3297,7 +3300,7 @@ static int chi2_launch(const void* A, int32_t dtype, int64_t n_orb, int64_t n_co
   if (ncol > 0) {
     double* part = (double*)ws;
     double* blk = (double*)(ws + a256((size_t)max_slabs * n_con * 8));
-    const int64_t rps = slab_rows(dtype, n_orb, ncol, max_slabs);
+    const int64_t rps = slab_rows(dtype, n_orb, ncol, max_slabs, 32);
     const int slabs = (int)((n_orb + rps - 1) / rps);
     const int64_t nb = (ncol + kChiCols - 1) / kChiCols;
     SW_HIP(wcolsum(A, dtype, n_orb, n_con, cb, ce, w, rps, slabs, part, nullptr, st));
@@ -3397,7 +3400,7 @@ extern "C" int model_observables(const void* A, int32_t dtype, int64_t n_orb, in
     return SW_OK;
   }
   SW_CHECK(A && w, "model_observables: null input");
-  const int64_t rps = slab_rows(dtype, n_orb, n_con, kSlabs);
+  const int64_t rps = slab_rows(dtype, n_orb, n_con, kSlabs, n_orb <= 512 ? 8 : 16);
   SW_HIP(wcolsum(A, dtype, n_orb, n_con, 0, n_con, w, rps, (int)((n_orb + rps - 1) / rps), nullptr, out, st));
   return SW_OK;
 }
