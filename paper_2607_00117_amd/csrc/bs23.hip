@@ -38,7 +38,7 @@
 //     the order in which the lanes add (repeated runs are identical to the bit);
 //     the rounding moves each weight by at most 2^-53, under 1e-12 of an entry
 //     over 5,000 steps.  The three blocks of a row are one histogram, so a row of
-//     up to 20,000 columns reads its events once: 30,000 rows of 19,541 columns
+//     up to 20,000 columns (10,000 of few steps) reads its events once: 30,000 rows of 19,541 columns
 //     took 6.2 ms in five passes, 4.0 now.
 #include <hip/hip_runtime.h>
 
@@ -56,6 +56,7 @@ extern int g_num_cus;
 namespace {
 
 constexpr int kBsWindow = 20000;  // histogram columns per pass (160,000 bytes of LDS)
+constexpr int kBsFewSteps = 64, kBsFewWindow = 10000;  // and for orbits of few steps, whose events cost little to read again
 constexpr int kRound = 8;          // attempts between two hand-overs
 constexpr int kBsThreads = 256;    // the integrating, the binning and two drift waves
 
@@ -392,19 +393,24 @@ bool shares_tile(int64_t tiles, int32_t n_steps, bool f64) {
 
 size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// rows that leave one workgroup per CU take 1,024 threads, shorter ones 256 (and
-// launches that 1,024 a row would bring to 2^32 threads)
+// Threads by the workgroups that a row's LDS leaves per CU: one or two take 1,024,
+// two to five 512, more 256 (fewer where a launch would reach 2^32 threads).
+// Calls of 100,000 orbits x 8 steps: rows of 5,198 columns 0.97 to 1.09 ms with 256
+// threads, 0.93 with 512; rows of 13,964 columns leave one workgroup per CU, in two
+// windows two: 2.70 and 2.42 ms.
 int hist_w(const uint64_t* ev_m, const uint64_t* ev_k, const double* wts, const double* ttot, int64_t n, int32_t S,
            const ObsK& O, int64_t n_con, double* A, double* overflow, double upsilon, hipStream_t st) {
   const int32_t nv = O.surface ? O.nv : 0;
-  for (int64_t w0 = 0; w0 < n_con; w0 += kBsWindow) {
-    const int32_t wn = (int32_t)(n_con - w0 < kBsWindow ? n_con - w0 : kBsWindow);
+  const int64_t win = S <= kBsFewSteps ? kBsFewWindow : kBsWindow;
+  for (int64_t w0 = 0; w0 < n_con; w0 += win) {
+    const int32_t wn = (int32_t)(n_con - w0 < win ? n_con - w0 : win);
     const size_t lds = (size_t)wn * 8;
     const auto go = [&](auto kernel, int nt) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(nt), lds, st, ev_m, ev_k, wts, ttot, S, O.ncopy, O.n_mass,
                          O.n_kin, nv, (int32_t)w0, wn, n_con, A, overflow, upsilon);
     };
     if (lds > 64 * 1024 && n < (int64_t)1 << 22) go(k_hist_w<1024>, 1024);
+    else if (lds > 32 * 1024 && n < (int64_t)1 << 23) go(k_hist_w<512>, 512);
     else go(k_hist_w<256>, 256);
     SW_HIP(hipGetLastError());
   }

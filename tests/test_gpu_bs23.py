@@ -217,3 +217,19 @@ def test_one_wave_per_tile_gives_the_bits_of_four(gpu, precision, comps, grid):
         part = gpu_bs23(cfg, obs, np.ascontiguousarray(ics[:, a:a + 20000]), dt[a:a + 20000], 3, 1e-6, 1e-8, precision)
         for g, p in zip(got, part):
             assert g[a:a + 20000].tobytes() == p.tobytes(), a
+
+
+@pytest.mark.parametrize("grid", [(10, 10, 10, 14, 10, 30), (13, 13, 13, 14, 14, 62), (17, 16, 15, 20, 20, 50)])
+@pytest.mark.parametrize("n_steps", [5, 64, 65])
+def test_row_lengths(gpu, grid, n_steps):
+    """Rows of 5,340, 14,545 and 24,480 columns (512 and 1,024 threads, one, two and three windows, which change at 64 steps)
+    against the oracle, with the surface block: the bars of the small-model test."""
+    cfg = W.SMALL
+    obs = dict(cfg["obs"], surface=1, upsilon=2.0, drift_every=3, **dict(zip(("nx", "ny", "nz", "npx", "npy", "nv"), grid)))
+    ics, dt = W.grid_ics(W.load_table(cfg["table"]), seed=7, n_steps=1000)
+    ics, dt = np.ascontiguousarray(ics[:, 100:165]), dt[100:165].copy()
+    A, ov, dr, fl = gpu_bs23(cfg, obs, ics, dt, n_steps, 1e-8, 1e-10)
+    A_o, ov_o, dr_o, fl_o = oracle_bs23(cfg, obs, ics, dt, n_steps, 1e-8, 1e-10)
+    assert A.shape[1] == grid[0] * grid[1] * grid[2] + grid[3] * grid[4] * (grid[5] + 1)
+    assert np.array_equal(fl, fl_o)
+    assert np.abs(A - A_o).max() <= 1e-8 and np.abs(ov - ov_o).max() <= 1e-8 and np.abs(dr - dr_o).max() <= 1e-9
