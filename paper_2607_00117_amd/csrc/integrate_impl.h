@@ -215,18 +215,22 @@ __device__ __forceinline__ void write_stage(const uint64_t (*stm)[OPW + 1], cons
 // CU, while workgroups of one wave may meet on one SIMD with others idle (the
 // barred model in FP64, 300 steps, 1,024 tiles: 8.3 ms in workgroups of one
 // tile, 5.1 of four).  At most 168 registers, so that three waves share a SIMD (the default
-// allocation lands one register above that, at two waves).  In FP64, and with
-// needle bars, more are live than that and 2 to 86 of them go to scratch, most of
-// them constants of the binning that a step reloads once: 100,000 FP64 orbits of
-// the barred model x 100 steps take 4.7 ms, on a cylindrical grid (42 spilled) 4.9;
-// binning one copy after the other (none and 12 spilled) they took 5.1 both.
+// allocation lands one register above that, at two waves); with needle bars, where
+// more are live, 14 to 46 of them go to scratch, most of them constants that a step
+// reloads once.  In FP64 the cylindrical grid's binning and constants held per lane
+// would spill up to 86: those forms take 212 to 256 registers and two waves a SIMD
+// (FP64, 300 orbits of 100 potentials of the barred model x 400 steps on a
+// cylindrical grid 7.7 ms with 168, 6.9 now, 7.5 before the branch-free binning;
+// 400,000 orbits x 20 of a point mass there 0.68 and 0.62, of the barred model with
+// the drift checked at each step 3.38 and 3.50).
 //
 // LPO lanes per orbit (1, or 2 in single precision): a wave carries 64 / LPO
 // orbits; the lanes of a pair hold the same state, each evaluates its share of
 // the force and the pair adds the shares, so both advance identically; the
 // first lane of the pair writes the orbit's events and results.
 template <typename T, int MODE, bool BIN, int LPO = 1, bool NB = false, bool CYL = false>
-__global__ __launch_bounds__(kTileWaves* kWave) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(kTileWaves* kWave)
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && BIN && (CYL || MODE == kPotOrbit) ? 2 : 3)))
 void k_integrate(const PotK p0, const sw_potential* __restrict__ pots, const int64_t* __restrict__ offsets,
                  int32_t n_pot, ObsK O, const T* __restrict__ ics, const T* __restrict__ dts, int64_t n_orb,
                  int64_t orb0, int64_t n_chunk, int32_t n_steps, uint64_t* __restrict__ ev_m,
