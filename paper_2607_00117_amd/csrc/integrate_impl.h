@@ -435,11 +435,21 @@ void launch_integrate_v(const IntegrateLaunch& L, hipStream_t st) {
   // adds at most a quarter to their number, and scalar constants leave their
   // waves free to share tiles (64 potentials of 2,000 FP32 orbits x 1,000 steps:
   // 10.9 ms lane by lane, 10.6 with scalar constants in one wave, 8.7 in two).
-  const int mode = L.n_pot == 1 ? kPotOne : (4 * (int64_t)L.n_pot <= full ? kPotTile : kPotOrbit);
+  int mode = L.n_pot == 1 ? kPotOne : (4 * (int64_t)L.n_pot <= full ? kPotTile : kPotOrbit);
   int64_t tiles = pair ? tile_count<32>(mode, L.n_pot, L.n_chunk) : tile_count<64>(mode, L.n_pot, L.n_chunk);
   int roles = 1;
   if (L.bin && !pair && mode != kPotOrbit && g_waves_per_cu == 0)
     roles = tiles <= (int64_t)kSplit3TilesPerCu * g_num_cus ? 3 : (sizeof(T) == 4 && !NB ? 2 : 1);
+  // One wave per tile: not where the cut tiles take one wave more per SIMD than
+  // the uncut ones (60 steps of the barred model in FP64, 65,000 orbits of 30
+  // potentials, 1,016 tiles or 1,046: 1.61 ms cut, 1.18 lane by lane; 120,000 of
+  // 100, 1,875 or 1,975 of 2,048: 1.79 and 1.85).  Pairs of lanes stay cut (32,000
+  // FP32 orbits of 30 potentials: 0.25 ms, 0.27 lane by lane).
+  const int64_t simds = (int64_t)kTileWaves * g_num_cus;
+  if (mode == kPotTile && roles == 1 && !pair && (tiles + simds - 1) / simds != (full + simds - 1) / simds) {
+    mode = kPotOrbit;
+    tiles = full;
+  }
   if (g_waves_per_cu > 0) {
     const int64_t cap = (int64_t)g_waves_per_cu * g_num_cus;
     if (tiles > cap) tiles = cap;
