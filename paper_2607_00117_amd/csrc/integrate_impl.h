@@ -420,11 +420,14 @@ extern int g_num_cus;
 // with the drift checked at each took 2.0 ms with one wave, 1.4 with two, 0.84
 // with three; 8,000 FP32 orbits of the barred model x 2,000 steps 5.3, 3.6, 3.6.
 // Above, two in single precision: 65,536 such orbits 10.0 -> 8.2 ms, 100,000 11.8
-// -> 10.8, 196,608 22.9 -> 21.6 (three: 8.3, 13.7, 23.2).  In double precision a
+// -> 10.8 (three: 8.3, 13.7), up to the seven tiles that a CU's LDS takes at once;
+// of more, some wait for a whole tile's steps (119,637 FP32 orbits x 300 steps:
+// 1.82 ms with two waves and 1.37 with one of two Plummer spheres on a cylindrical
+// grid, 1.61 and 1.35 of the barred model).  In double precision a
 // wave fills its SIMD, and integrating waves that share one lose more than the
 // others give (the barred model, 768 tiles x 300 steps: 5.2 ms with one wave, 7.1
 // with two); needle bars need more registers than two waves per tile leave.
-constexpr int kSplit3TilesPerCu = 2;
+constexpr int kSplit3TilesPerCu = 2, kSplit2TilesPerCu = 7;
 
 template <typename T, bool NB, bool CYL>
 void launch_integrate_v(const IntegrateLaunch& L, hipStream_t st) {
@@ -438,8 +441,10 @@ void launch_integrate_v(const IntegrateLaunch& L, hipStream_t st) {
   int mode = L.n_pot == 1 ? kPotOne : (4 * (int64_t)L.n_pot <= full ? kPotTile : kPotOrbit);
   int64_t tiles = pair ? tile_count<32>(mode, L.n_pot, L.n_chunk) : tile_count<64>(mode, L.n_pot, L.n_chunk);
   int roles = 1;
-  if (L.bin && !pair && mode != kPotOrbit && g_waves_per_cu == 0)
-    roles = tiles <= (int64_t)kSplit3TilesPerCu * g_num_cus ? 3 : (sizeof(T) == 4 && !NB ? 2 : 1);
+  if (L.bin && !pair && mode != kPotOrbit && g_waves_per_cu == 0) {
+    if (tiles <= (int64_t)kSplit3TilesPerCu * g_num_cus) roles = 3;
+    else if (sizeof(T) == 4 && !NB && tiles <= (int64_t)kSplit2TilesPerCu * g_num_cus) roles = 2;
+  }
   // One wave per tile: not where the cut tiles take one wave more per SIMD than
   // the uncut ones (60 steps of the barred model in FP64, 65,000 orbits of 30
   // potentials, 1,016 tiles or 1,046: 1.61 ms cut, 1.18 lane by lane; 120,000 of
