@@ -28,8 +28,8 @@
 //     30,000 x 5,000 steps of the barred model in FP32: 107.5 ms in one wave with
 //     common steps, 44.9 now (54.9 with one drift wave, 46.7 without a raised
 //     priority for the integrating waves).
-//     FP64 and needle-bar launches of more tiles than the CUs hold of these
-//     workgroups take one wave per tile (k_bs23_one; shares_tile has the figures).
+//     Launches of many more tiles than the CUs hold of these workgroups take one
+//     wave per tile (k_bs23_one; shares_tile has the rule and its figures).
 //  2. k_hist_w: one workgroup per orbit (and window of columns when a row does
 //     not fit LDS): each event's weight dt_k / t_total is rounded to a 64-bit
 //     fixed-point integer in units of 2^-52 and added into an LDS histogram of
@@ -374,21 +374,25 @@ __global__ __launch_bounds__(NT) void k_hist_w(const uint64_t* __restrict__ ev_m
   if (tid < 2 && win0 == 0) overflow[o * 2 + tid] = (double)ovq[tid] * scale;
 }
 
-// Whether four waves share a tile, where two such workgroups fit a CU (FP64, and
-// needle bars).  Up to two tiles per CU they are all resident, and do.  Above, the
-// next round waits, while one wave per tile still leaves a wave its SIMD up to
-// four tiles per CU and two waves share one up to eight; the tiles of a workgroup
-// are spread over the SIMDs.  40 steps of the barred model in FP64, four waves and
-// one: 32,700 orbits 2.7 and 5.0 ms, 65,500 5.2 and 5.1, 98,000 7.6 and 8.4,
-// 131,000 10.2 and 8.5, 200,000 16.9 and 15.6.  In single precision with needle
-// bars the three forces cost less next to the rest: 65,500 orbits 5.9 and 6.8, and
-// of 4 steps 1.3 and 1.2.  A few steps per orbit leave the hand-over's first and
-// last rounds: 98,000 FP64 orbits x 4 steps 1.5 and 1.3.
-bool shares_tile(int64_t tiles, int32_t n_steps, bool f64) {
+// Whether four waves share a tile.  Where the CUs hold all of these workgroups
+// (three a CU in single precision, two in double and with needle bars) they do.
+// Of more, some wait, while one wave per tile leaves a wave its SIMD up to four
+// tiles per CU and two waves share one up to eight; the tiles of a workgroup are
+// spread over the SIMDs.  40 steps of the barred model in FP64, four waves and one:
+// 32,700 orbits 2.7 and 5.0 ms, 65,500 5.2 and 5.1, 131,000 10.2 and 8.5; 70,000 x
+// 32 steps of three discs 0.71 and 0.61.  In single precision a second round of
+// workgroups pays from some 32 steps on, and a third where the drift is evaluated
+// at each step (the wave that the drift is taken from has the more to do): the
+// barred model, 70,000 orbits x 300 steps 5.6 and 7.9 ms, 140,000 with each step's
+// drift 9.8 and 12.5; three discs, 200,000 x 68 1.66 and 1.25.  With needle bars a
+// second and a third round pay with each step's drift only: 44,000 orbits x 32
+// steps 4.1 and 4.8 ms, with that of every tenth step 3.6 and 3.0.
+bool shares_tile(int64_t tiles, int32_t n_steps, bool f64, bool needle, int32_t drift_every) {
   const int64_t cus = g_num_cus;
-  if (tiles <= 2 * cus) return true;
-  if (tiles <= 4 * cus) return !f64 && n_steps >= 16;
-  return tiles <= 6 * cus && n_steps >= 32;
+  const bool each = drift_every == 1;
+  if (f64) return tiles <= 2 * cus;
+  if (needle) return tiles <= 2 * cus || (each && ((tiles <= 4 * cus && n_steps >= 16) || (tiles <= 6 * cus && n_steps >= 32)));
+  return tiles <= 3 * cus || (tiles <= (each ? 9 : 6) * cus && n_steps >= 32);
 }
 
 size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -462,14 +466,12 @@ extern "C" int integrate_bs23_and_bin(const sw_potential* pot, const double* ics
       hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(nt), 0, st, P, O, ics, h0, n_orb, n_steps, rtol, atol,
                          ev_m, ev_k, wts, ttot, drift, flags);
     };
-    if constexpr (sizeof(T) == 8 || NB) {
-      if (!shares_tile(tiles, n_steps, sizeof(T) == 8)) {
-        const int64_t nw = std::min<int64_t>(4, (tiles + g_num_cus - 1) / g_num_cus);
-        go(k_bs23_one<T, NB, CYL>, (tiles + nw - 1) / nw, (int)nw * 64);
-        return;
-      }
+    if (shares_tile(tiles, n_steps, sizeof(T) == 8, NB, O.drift_every)) {
+      go(k_bs23<T, NB, CYL>, tiles, kBsThreads);
+    } else {
+      const int64_t nw = std::min<int64_t>(4, (tiles + g_num_cus - 1) / g_num_cus);
+      go(k_bs23_one<T, NB, CYL>, (tiles + nw - 1) / nw, (int)nw * 64);
     }
-    go(k_bs23<T, NB, CYL>, tiles, kBsThreads);
   };
   const auto with_bars = [&](auto t, auto cyl) {
     if (nb) launch(t, std::true_type{}, cyl);

@@ -195,7 +195,7 @@ def test_single_precision_small_model(gpu):
     assert np.allclose(A[:, 1000:1750].sum(1) + ov[:, 1], 1.0, rtol=0, atol=1e-11)
 
 
-@pytest.mark.parametrize("precision,comps", [(2, None), (1, "needle"), (2, "needle")])
+@pytest.mark.parametrize("precision,comps", [(1, None), (2, None), (1, "needle"), (2, "needle")])
 @pytest.mark.parametrize("grid", ["cartesian", "cylindrical"])
 def test_one_wave_per_tile_gives_the_bits_of_four(gpu, precision, comps, grid):
     """99,001 orbits fill more than the CUs' four-wave workgroups and take one wave per 64 orbits in workgroups of four
