@@ -221,16 +221,18 @@ __device__ __forceinline__ void write_stage(const uint64_t (*stm)[OPW + 1], cons
 // would spill up to 86: those forms take 212 to 256 registers and two waves a SIMD
 // (FP64, 300 orbits of 100 potentials of the barred model x 400 steps on a
 // cylindrical grid 7.7 ms with 168, 6.9 now, 7.5 before the branch-free binning;
-// 400,000 orbits x 20 of a point mass there 0.68 and 0.62, of the barred model with
-// the drift checked at each step 3.38 and 3.50).
+// 400,000 orbits x 500 of a point mass there 8.4 and 7.4).  On that grid the form
+// of three waves (THREE) is left for the launches whose tiles all reside with it
+// and not with two (133,000 such orbits 3.1 ms with three, 3.5 with two; with
+// needle bars both take the same time).
 //
 // LPO lanes per orbit (1, or 2 in single precision): a wave carries 64 / LPO
 // orbits; the lanes of a pair hold the same state, each evaluates its share of
 // the force and the pair adds the shares, so both advance identically; the
 // first lane of the pair writes the orbit's events and results.
-template <typename T, int MODE, bool BIN, int LPO = 1, bool NB = false, bool CYL = false>
+template <typename T, int MODE, bool BIN, int LPO = 1, bool NB = false, bool CYL = false, bool THREE = false>
 __global__ __launch_bounds__(kTileWaves* kWave)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && BIN && (CYL || MODE == kPotOrbit) ? 2 : 3)))
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && BIN && ((CYL && !THREE) || MODE == kPotOrbit) ? 2 : 3)))
 void k_integrate(const PotK p0, const sw_potential* __restrict__ pots, const int64_t* __restrict__ offsets,
                  int32_t n_pot, ObsK O, const T* __restrict__ ics, const T* __restrict__ dts, int64_t n_orb,
                  int64_t orb0, int64_t n_chunk, int32_t n_steps, uint64_t* __restrict__ ev_m,
@@ -493,6 +495,12 @@ void launch_integrate_v(const IntegrateLaunch& L, hipStream_t st) {
     if constexpr (sizeof(T) == 4 && !NB) {
       if (roles == 2) {
         split(k_integrate_split<T, M, 2, NB, CYL>);
+        return;
+      }
+    }
+    if constexpr (sizeof(T) == 8 && CYL && !NB) {
+      if (tiles > 2 * simds && tiles <= 3 * simds) {
+        one(k_integrate<T, M, true, 1, NB, CYL, true>);
         return;
       }
     }

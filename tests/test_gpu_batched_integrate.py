@@ -284,9 +284,9 @@ def test_waves_sharing_a_tile_give_the_bits_of_one_wave(gpu, offsets, n_steps, e
 
 # more tiles than three waves share, as one potential and as ragged ones with tiles of their own; 45 potentials of 88
 # orbits, one per lane, and 26 of 2,500, whose own tiles would take a wave more per SIMD; more tiles than reside in
-# workgroups of two waves; cylindrical grids and needle bars throughout
+# workgroups of two waves, or two to a SIMD; cylindrical grids and needle bars throughout
 @pytest.mark.parametrize("offsets", [[0, 33000], [0, 20011, 33100], list(range(0, 45 * 88 + 1, 88)),
-                                     list(range(0, 26 * 2500 + 1, 2500)), [0, 115000]])
+                                     list(range(0, 26 * 2500 + 1, 2500)), [0, 133000]])
 @pytest.mark.parametrize("grid", ["cartesian", "cylindrical"])
 @pytest.mark.parametrize("needle", [False, True])
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
