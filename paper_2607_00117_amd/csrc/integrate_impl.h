@@ -216,13 +216,13 @@ __device__ __forceinline__ void write_stage(const uint64_t (*stm)[OPW + 1], cons
 // barred model in FP64, 300 steps, 1,024 tiles: 8.3 ms in workgroups of one
 // tile, 5.1 of four).  At most 168 registers, so that three waves share a SIMD (the default
 // allocation lands one register above that, at two waves); with needle bars, where
-// more are live, 14 to 46 of them go to scratch, most of them constants that a step
+// more are live, 14 to 41 of them go to scratch, most of them constants that a step
 // reloads once.  In FP64 the cylindrical grid's binning and constants held per lane
-// would spill up to 86: those forms take 212 to 256 registers and two waves a SIMD
+// would spill up to 86: those forms take 184 to 256 registers and two waves a SIMD
 // (FP64, 300 orbits of 100 potentials of the barred model x 400 steps on a
 // cylindrical grid 7.7 ms with 168, 6.9 now, 7.5 before the branch-free binning;
 // 400,000 orbits x 500 of a point mass there 8.4 and 7.4).  On that grid the form
-// of three waves (THREE) is left for the launches whose tiles all reside with it
+// of three waves (THREE, 42 spilled) is left for the launches whose tiles all reside with it
 // and not with two (133,000 such orbits 3.1 ms with three, 3.5 with two; with
 // needle bars both take the same time).
 //
